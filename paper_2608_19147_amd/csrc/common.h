@@ -89,6 +89,7 @@ struct GemvArgs {
 // Prefill product (gemm_pf_kernel): W [N][K] (tiled) times the prepared rows of
 // n tokens, kept as 64-row blocks of the prepared-operand layout (block b at
 // bp + b * bp_blk halves, its corrections at bc + b * bc_blk floats).
+constexpr int PF_BAND = 8;                        // token blocks that run side by side (gemm_pf_kernel)
 struct PfArgs {
     PackedMat W;
     const uint16_t* bp; const float* bc; size_t bp_blk, bc_blk;

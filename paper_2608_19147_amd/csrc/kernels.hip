@@ -933,6 +933,14 @@ hipError_t launch_gemm_bp(const GemvArgs& a, hipStream_t st) {
 
 // ------------------------------------------------------------------ prefill product
 
+// A bounds-checked buffer over `bytes` at p (loads past the end return zero).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t attn_rsrc(const void* p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ u32x4 pf_load16(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t soff) {
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0));
+}
+
 // Prepared rows of a prompt: row r of `in` goes to row r mod 64 of block r / 64
 // (blocks of 64 * kp codes and 2 * kp corrections).  With gamma, the row is
 // RMS-normalized first (its squares added in one fixed order by every slice);
@@ -982,161 +990,195 @@ hipError_t launch_bprep_rows(const void* in, int in_dt, int in_ld, const uint16_
 
 // Product of a prompt's prepared rows with one matrix.  A workgroup takes four
 // 64-row weight tiles (one per wave) and one 64-token block, over all of K.
-// Per group of 128 k: the block's 16 operand fragments (16 KB) are copied into
-// LDS by direct loads (each wave four of them) and shared by the four waves;
-// each wave decodes its tile's codes into the A operands of
-// v_mfma_f32_16x16x32_f16 exactly as gemm_bp_kernel does, and adds
-// scale * (products - correction) per row and group.  The next group's
-// fragments and codes are loaded while a group computes (two LDS buffers, two
-// register sets).  Workgroups are numbered so that those sharing a weight tile
-// group run on the same XCD one after the other (its L2 keeps the tiles while
-// the token blocks sweep past).
-template <int DUMMY>
-__global__ __launch_bounds__(256, 1) void gemm_pf_kernel(PfArgs a) {
-    __shared__ __attribute__((aligned(16))) uint16_t sb[2][16][64][8];
+// Per group of 128 k the block's 16 operand fragments (16 KB) go through
+// registers into LDS (two buffers) and are shared by the four waves; each wave
+// decodes its tile's codes into matrix-core operands as gemm_bp_kernel does.
+// The products are taken transposed (tokens as the rows, weight rows as the
+// columns): a lane's results are four tokens of one weight row, so a row's
+// scale is one register, and the corrections of four tokens are the products'
+// starting value (one 16-byte LDS read), which leaves one multiply-add per
+// result and group.  The next group's codes and the one after's fragments are
+// in flight while a group computes.
+// RAG: K is not a multiple of 128 (operand entries past K are dropped).
+template <bool RAG>
+__global__ __launch_bounds__(256, 2) void gemm_pf_kernel(PfArgs a) {
+    __shared__ __attribute__((aligned(16))) u32x4 sb[2][16][64];
+    __shared__ __attribute__((aligned(16))) float sc[2][64];
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lg = lane >> 4;
+    // workgroups of one XCD (blockIdx mod 8) walk the tiles in bands of PF_BAND
+    // token blocks: the 64 that run at once share 8 weight tile groups and 8
+    // token blocks in the XCD's L2
     const int total = a.nwt * a.ntb;
     const int per_xcd = (total + 7) / 8;
     const int q = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-    if (q >= total) return;                                    // whole workgroup: no barrier is reached
-    const int wt = q / a.ntb, tb = q % a.ntb;
+    if ((int)(blockIdx.x >> 3) >= per_xcd || q >= total) return;   // whole workgroup: no barrier is reached
+    const int band = q / (PF_BAND * a.nwt), inb = q - band * PF_BAND * a.nwt;
+    const int bw = min(PF_BAND, a.ntb - band * PF_BAND);
+    const int wt = inb / bw, tb = band * PF_BAND + inb % bw;
     const PackedMat W = a.W;
     const int t = 4 * wt + w;
     const bool has = t < W.ntiles;
     const int tt = has ? t : W.ntiles - 1;                     // loads stay in bounds; results are dropped
     const int K = W.k;
     const int ng = (K + 127) / 128;
-    const uint16_t* bpb = a.bp + (size_t)tb * a.bp_blk;
-    const float* bcb = a.bc + (size_t)tb * a.bc_blk;
+    // buffer resources: uniform group offsets, one 32-bit offset per lane
+    const __amdgpu_buffer_rsrc_t rbp = attn_rsrc(a.bp + (size_t)tb * a.bp_blk, (uint32_t)a.bp_blk * 2);
+    const __amdgpu_buffer_rsrc_t rbc = attn_rsrc(a.bc + (size_t)tb * a.bc_blk, (uint32_t)a.bc_blk * 4);
+    const __amdgpu_buffer_rsrc_t rw = attn_rsrc(W.w + (size_t)tt * W.nchunk * 1024, (uint32_t)W.nchunk * 1024);
+    const __amdgpu_buffer_rsrc_t rs = attn_rsrc(W.s + (size_t)tt * W.ngroups * 64, (uint32_t)W.ngroups * 128);
+    const uint32_t bo = 16u * tid, co = 4u * tid, wo = 16u * (64 * lg + l16), so = 2u * l16;
     uint32_t magic = 0x64006400u;
     asm volatile("" : "+v"(magic));
 
-    // one group's operand fragments into LDS buffer `buf`: fragment 4 w + u by wave w
-    auto stage_b = [&](int g, int buf) {
+    u32x4 rb[4];
+    float rc;
+    // one group's operand fragments (fragment 4 u + w by wave w) and corrections
+    // (thread 4 r + c: chunk c of token r)
+    auto ld_b = [&](int g) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) rb[u] = pf_load16(rbp, bo, 16384 * g + 4096 * u);
+        rc = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rbc, co, 1024 * g, 0));
+    };
+    auto st_b = [&](int g) {
+        const int buf = g & 1;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int f = 4 * w + u;
-            __builtin_amdgcn_global_load_lds(bpb + (((size_t)g * 16 + f) * 64 + lane) * 8,
-                                             (__attribute__((address_space(3))) void*)&sb[buf][f][0][0], 16, 0, 0);
+            u32x4 v = rb[u];
+            if constexpr (RAG) {                               // fragment f = 4 cb + i holds k = 32 lg + 8 i + e
+                const bool in = 128 * g + 32 * lg + 8 * w < K;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = in ? v[e] : 0u;
+            }
+            sb[buf][4 * u + w][lane] = v;
         }
+        float s = rc;
+        if constexpr (RAG) s = 128 * g + 32 * (tid & 3) < K ? s : 0.f;
+        s += dpp_f<0xB1>(s);                                   // lane ^ 1
+        s += dpp_f<0x4E>(s);                                   // lane ^ 2: the token's 4 chunks
+        sc[buf][tid >> 2] = -s;                                // the same value from 4 lanes
     };
-    // codes and scales of the wave's tile, and the corrections of the block's
-    // tokens (summed over the group's valid chunks), for group g
-    auto ld_w = [&](int g, u32x4 (&wv)[4], u32x2 (&sv)[4], float (&cs)[4]) {
+    u32x4 cw[4];
+    uint16_t cs[4];
+    auto ld_w = [&](int g, int rt) {
+        cw[rt] = pf_load16(rw, wo, 4096 * g + 256 * rt);
+        cs[rt] = __builtin_amdgcn_raw_buffer_load_b16(rs, so, 128 * g + 32 * rt, 0);
+    };
+    auto decode = [&](const u32x4& v, half8_t (&B)[4]) {
 #pragma unroll
-        for (int rt = 0; rt < 4; ++rt) {
-            wv[rt] = __builtin_nontemporal_load((const u32x4*)(W.w + (((size_t)tt * W.nchunk + 4 * g + lg) * 64 + 16 * rt + l16) * 16));
-            sv[rt] = *(const u32x2*)(W.s + ((size_t)tt * W.ngroups + g) * 64 + 16 * rt + 4 * lg);
-        }
-        const int kb = 128 * g;
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb) {
-            const float4 c4 = *(const float4*)(bcb + ((size_t)g * 64 + 16 * cb + l16) * 4);
-            cs[cb] = ((kb < K ? c4.x : 0.f) + (kb + 32 < K ? c4.y : 0.f)) + ((kb + 64 < K ? c4.z : 0.f) + (kb + 96 < K ? c4.w : 0.f));
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t x = v[i], y = x >> 8;
+            u32x4 av;
+            av[0] = and_or_u32(0x000F000Fu, x, magic);
+            av[1] = and_or_u32(0x00F000F0u, x, magic);
+            av[2] = and_or_u32(0x000F000Fu, y, magic);
+            av[3] = and_or_u32(0x00F000F0u, y, magic);
+            B[i] = __builtin_bit_cast(half8_t, av);
         }
     };
 
-    f32x4_t acc[4][4];
+    f32x4_t acc[4][4], c[2][4];
+    half8_t A[4][4], B[2][4];
+    float scl[2];
 #pragma unroll
     for (int rt = 0; rt < 4; ++rt)
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) acc[rt][cb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-    u32x4 cw[4], nw[4];
-    u32x2 cs2[4], ns2[4];
-    float cc[4], nc[4];
-    stage_b(0, 0);
-    ld_w(0, cw, cs2, cc);
+    ld_b(0);
+#pragma unroll
+    for (int rt = 0; rt < 4; ++rt) ld_w(0, rt);
+    st_b(0);
+    ld_b(min(1, ng - 1));
+    __syncthreads();
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) A[cb][i] = __builtin_bit_cast(half8_t, sb[0][4 * cb + i][lane]);
+        c[0][cb] = *(const f32x4_t*)&sc[0][16 * cb + 4 * lg];
+        c[1][cb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
+    decode(cw[0], B[0]);
+    scl[0] = f16_to_f32(cs[0]);
+    scl[1] = 0.f;
+    ld_w(min(1, ng - 1), 0);
+    // One group in four steps of one 16-row weight block: 16 products, k slice by
+    // k slice over four independent token blocks.  While a step's products run, the
+    // step before's results are scaled into the sums and its registers reloaded with
+    // the next starting values, and the next step's codes are decoded (and their
+    // registers reloaded with the next group's).  Step 1 fills the other LDS buffer;
+    // the barrier at step 3 opens it (by then every wave holds all of this group's
+    // operands and corrections), and step 3 replaces each token operand after its
+    // last product.  Past the last group the loads repeat it and what they feed is
+    // not used.
     for (int g = 0; g < ng; ++g) {
-        const int buf = g & 1;
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wave's copies and loads of group g are done
-        __syncthreads();                                        // and every wave's; the other buffer is free
-        const bool more = g + 1 < ng;
-        if (more) {                                             // group g + 1 loads while group g computes
-            stage_b(g + 1, buf ^ 1);
-            ld_w(g + 1, nw, ns2, nc);
-        }
-        const int kb = 128 * g;
-        half8_t A[4][4];
-        float scl[4][4];
+        const int buf = g & 1, gn = min(g + 1, ng - 1);
 #pragma unroll
         for (int rt = 0; rt < 4; ++rt) {
+            const int p = rt & 1;
+            __builtin_amdgcn_sched_barrier(0);
+            if (rt == 1) {
+                st_b(g + 1);
+                ld_b(min(g + 2, ng - 1));
+            }
+            if (rt == 3) __syncthreads();
+            decode(cw[(rt + 1) & 3], B[p ^ 1]);
+            const float sp = scl[p ^ 1];
+            scl[p ^ 1] = f16_to_f32(cs[(rt + 1) & 3]);
+            ld_w(rt < 3 ? gn : min(g + 2, ng - 1), (rt + 1) & 3);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint32_t x = cw[rt][i], y = x >> 8;
-                u32x4 av;
-                av[0] = and_or_u32(0x000F000Fu, x, magic);
-                av[1] = and_or_u32(0x00F000F0u, x, magic);
-                av[2] = and_or_u32(0x000F000Fu, y, magic);
-                av[3] = and_or_u32(0x00F000F0u, y, magic);
-                A[rt][i] = __builtin_bit_cast(half8_t, av);
+            for (int cb = 0; cb < 4; ++cb) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[(rt + 3) & 3][cb][j] = __builtin_fmaf(sp, c[p ^ 1][cb][j], acc[(rt + 3) & 3][cb][j]);
+                c[p ^ 1][cb] = *(const f32x4_t*)&sc[rt < 3 ? buf : buf ^ 1][16 * cb + 4 * lg];
             }
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-                const uint32_t h = cs2[rt][jj >> 1];
-                scl[rt][jj] = f16_to_f32((uint16_t)((jj & 1) ? (h >> 16) : (h & 0xFFFFu)));
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb) {
+                    c[p][cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[cb][i], B[p][i], c[p][cb], 0, 0, 0);
+                    if (rt == 3) A[cb][i] = __builtin_bit_cast(half8_t, sb[buf ^ 1][4 * cb + i][lane]);
+                }
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
             }
-        }
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb) {
-            u32x4 B[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                B[i] = *(const u32x4*)&sb[buf][4 * cb + i][lane][0];
-                const bool in = kb + 32 * lg + 8 * i < K;          // past the end of a ragged last group: dropped
-#pragma unroll
-                for (int e = 0; e < 4; ++e) B[i][e] = in ? B[i][e] : 0u;
-            }
-#pragma unroll
-            for (int rt = 0; rt < 4; ++rt) {
-                f32x4_t c = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    c = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[rt][i], __builtin_bit_cast(half8_t, B[i]), c, 0, 0, 0);
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) acc[rt][cb][jj] = __builtin_fmaf(scl[rt][jj], c[jj] - cc[cb], acc[rt][cb][jj]);
-            }
-        }
-        if (more) {
-#pragma unroll
-            for (int rt = 0; rt < 4; ++rt) {
-                cw[rt] = nw[rt];
-                cs2[rt] = ns2[rt];
-            }
-#pragma unroll
-            for (int cb = 0; cb < 4; ++cb) cc[cb] = nc[cb];
         }
     }
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[3][cb][j] = __builtin_fmaf(scl[1], c[1][cb][j], acc[3][cb][j]);
     if (!has) return;
 
-    // ---- epilogue: lane holds rows 64 t + 16 rt + 4 lg + j of token 64 tb + 16 cb + l16
+    // ---- epilogue: lane holds row 64 t + 16 rt + l16 of tokens 64 tb + 16 cb + 4 lg + j
     if (a.epi == EPI_SWIGLU) {                                 // rows 0..31 of a tile gate, 32..63 the matching up
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-            for (int cb = 0; cb < 4; ++cb) {
-                const int tok = 64 * tb + 16 * cb + l16;
+            for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const int f = 32 * t + 16 * rt + 4 * lg + j;
+                    const int tok = 64 * tb + 16 * cb + 4 * lg + j;
+                    const int f = 32 * t + 16 * rt + l16;
                     if (tok < a.n && f < a.n_valid) {
                         const float gt = acc[rt][cb][j], up = acc[rt + 2][cb][j];
                         a.out[(size_t)tok * a.out_ld + f] = (gt / (1.0f + expf(-gt))) * up;
                     }
                 }
-            }
         return;
     }
 #pragma unroll
-    for (int rt = 0; rt < 4; ++rt)
+    for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb) {
-            const int tok = 64 * tb + 16 * cb + l16;
+        for (int j = 0; j < 4; ++j) {
+            const int tok = 64 * tb + 16 * cb + 4 * lg + j;
+            if (tok >= a.n) continue;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int row = 64 * t + 16 * rt + 4 * lg + j;
-                if (tok >= a.n || row >= W.n) continue;
+            for (int rt = 0; rt < 4; ++rt) {
+                const int row = 64 * t + 16 * rt + l16;
+                if (row >= W.n) continue;
                 float v = acc[rt][cb][j];
                 if (a.epi == EPI_RESID) {
                     v += load_val(a.resid, a.resid_dt, (size_t)tok * a.resid_ld + row);
@@ -1151,7 +1193,8 @@ hipError_t launch_gemm_pf(const PfArgs& a, hipStream_t st) {
     if (a.n < 1 || a.W.gchunks != 4 || a.nwt != (a.W.ntiles + 3) / 4 || a.ntb != (a.n + 63) / 64) return hipErrorInvalidValue;
     const int total = a.nwt * a.ntb;
     const unsigned grid = 8u * (unsigned)((total + 7) / 8);
-    gemm_pf_kernel<0><<<dim3(grid), dim3(256), 0, st>>>(a);
+    if (a.W.k % 128) gemm_pf_kernel<true><<<dim3(grid), dim3(256), 0, st>>>(a);
+    else gemm_pf_kernel<false><<<dim3(grid), dim3(256), 0, st>>>(a);
     return hipGetLastError();
 }
 
@@ -1868,9 +1911,6 @@ constexpr int ATTN_NB = 4;                // step buffers (K and V of 32 keys ea
 constexpr int ATTN_SCH = 1024;            // most keys of one split on this path
 constexpr int ATTN_RSM = 8192;            // bytes of per-query-row mask staged per split (rows x split keys)
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t attn_rsrc(const void* p, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
-}
 __device__ __forceinline__ void attn_dma(__amdgpu_buffer_rsrc_t r, uint32_t off, void* lds) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, off, 0, 0, 2 /* nt */);
 }

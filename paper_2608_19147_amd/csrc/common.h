@@ -95,11 +95,28 @@ struct PfArgs {
     const uint16_t* bp; const float* bc; size_t bp_blk, bc_blk;
     int n;                                         // tokens
     int epi;                                       // EPI_STORE, EPI_RESID, EPI_SWIGLU
-    float* out; int out_ld;                        // STORE: out; RESID: new x; SWIGLU: act (fp32)
+    float* out; int out_ld;                        // STORE: out; RESID: new x
+    uint16_t* bp_out; float* bc_out;               // SWIGLU: the down product's input, 64-row blocks
+    size_t out_bp_blk, out_bc_blk;
     const void* resid; int resid_dt; int resid_ld; // RESID source (may be out itself)
     void* out_act; int out_act_dt; int out_act_ld; // RESID: optional copy in the act dtype
     int n_valid;                                   // SWIGLU: F
     int nwt, ntb;                                  // groups of 4 weight tiles, 64-token blocks
+    int ksplit, kg;                                // splits of K (RESID only if more than one), groups of 128 k per split
+    float* part; size_t part_stride;               // ksplit > 1: the splits' sums [ksplit][n][out_ld], not yet added to resid
+};
+
+// Rows of a prompt between two products (bprep_rows_kernel): x = in + the
+// nsplit partial sums of the product before; RMSNorm(x) * gamma in prepared
+// 64-row blocks (bp null: only x).
+struct PfRows {
+    const void* in; int in_dt; int in_ld;          // [n][K]
+    const float* part; int nsplit; size_t part_stride;
+    float* x_out;                                  // optional [n][K]: x
+    void* out_act; int out_act_dt;                 // optional [n][K]: x in the act dtype
+    const uint16_t* gamma; int gamma_dt;
+    int K; float eps; int n;
+    uint16_t* bp; float* bc; int kp;
 };
 
 struct AttnArgs {
@@ -284,10 +301,7 @@ hipError_t launch_gemm_pf(const PfArgs& a, hipStream_t st);
 // (layer 0 only, else nullptr) marks the rows as the slot's own.
 hipError_t launch_kv_rope_append(const float* qkv, int ld, const int* pos, const float2* rope, int n, int P, int Hq, int Hkv,
                                  int D, uint16_t* kl, uint16_t* vl, int cap, int16_t* table, int kv_dt, hipStream_t st);
-// Rows [0, n) of `in` (fp32 or half, row stride in_ld) to 64-row prepared blocks:
-// gamma != nullptr: RMSNorm(row) * gamma (full normalization); nullptr: the row as it is.
-hipError_t launch_bprep_rows(const void* in, int in_dt, int in_ld, const uint16_t* gamma, int gamma_dt, int K, float eps,
-                             int n, uint16_t* bp, float* bc, int kp, hipStream_t st);
+hipError_t launch_bprep_rows(const PfRows& a, hipStream_t st);
 hipError_t launch_dequant(const PackedMat& m, int row_off, int row_map, int n_rows, float* out, hipStream_t st);
 // Rows src[b][i] (< 0: zero padding) of every slot's logical view, read through
 // `table`, to dst [L][S][Hkv][dst_stride][D] rows i < Pn.

@@ -941,50 +941,136 @@ __device__ __forceinline__ u32x4 pf_load16(__amdgpu_buffer_rsrc_t r, uint32_t of
     return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0));
 }
 
-// Prepared rows of a prompt: row r of `in` goes to row r mod 64 of block r / 64
-// (blocks of 64 * kp codes and 2 * kp corrections).  With gamma, the row is
-// RMS-normalized first (its squares added in one fixed order by every slice);
-// without, it is taken as it is.  One workgroup per (row, slice of 1024 k).
-__global__ __launch_bounds__(256) void bprep_rows_kernel(const void* in, int in_dt, int in_ld, const uint16_t* gamma,
-                                                         int gamma_dt, int K, float eps, uint16_t* bp, float* bc, int kp) {
-    constexpr int SPT = BPREP_SLICE / 256;
-    __shared__ float red[4];
-    const int r = blockIdx.x, tid = threadIdx.x, k0 = BPREP_SLICE * blockIdx.y;
-    uint16_t* bpb = bp + (size_t)(r >> 6) * 64 * kp;
-    float* bcb = bc + (size_t)(r >> 6) * 2 * kp;
-    float rs = 1.f;
-    if (gamma) {
-        float ss = 0.f;
-        for (int k0b = 0; k0b < K; k0b += 256 * 8) {
-            float v[8];
+// Eight consecutive values at element offset i of p (fp32 at 16-byte aligned
+// offsets; 16-bit values at any 2-byte aligned address).
+__device__ __forceinline__ void load8(const void* p, int dt, size_t i, float (&v)[8]) {
+    if (dt == DT_F32) {
+        float4 x[2];
+        x[0] = *(const float4*)((const float*)p + i);
+        x[1] = *(const float4*)((const float*)p + i + 4);
+        __builtin_memcpy(v, x, 32);
+    } else {
+        uint16_t h[8];
+        __builtin_memcpy(h, (const uint16_t*)p + i, 16);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int k = k0b + tid + 256 * i;
-                v[i] = load_val(in, in_dt, (size_t)r * in_ld + min(k, K - 1));
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) ss += (k0b + tid + 256 * i < K) ? v[i] * v[i] : 0.f;
-        }
-        ss = wave_sum_all(ss);
-        if ((tid & 63) == 0) red[tid >> 6] = ss;
-        __syncthreads();
-        rs = rsqrtf(((red[0] + red[1]) + (red[2] + red[3])) / (float)K + eps);
-    }
-#pragma unroll
-    for (int i = 0; i < SPT; ++i) {
-        const int k = k0 + tid + 256 * i;
-        const int kc = min(k, K - 1);
-        const float x = load_val(in, in_dt, (size_t)r * in_ld + kc);
-        const float g = gamma ? half_bits_to_f32(gamma[kc], gamma_dt) : 1.f;
-        if (k0 + 256 * i < K) bp_put(bpb, bcb, kp, r & 63, k, x * rs * g, k < K);   // whole 32-lane groups
+        for (int e = 0; e < 8; ++e) v[e] = dt == DT_BF16 ? bf16_to_f32(h[e]) : f16_to_f32(h[e]);
     }
 }
 
-hipError_t launch_bprep_rows(const void* in, int in_dt, int in_ld, const uint16_t* gamma, int gamma_dt, int K, float eps,
-                             int n, uint16_t* bp, float* bc, int kp, hipStream_t st) {
-    if (K < 1 || n < 1 || kp < K || kp % 128) return hipErrorInvalidValue;
-    bprep_rows_kernel<<<dim3(n, (K + BPREP_SLICE - 1) / BPREP_SLICE), 256, 0, st>>>(in, in_dt, in_ld, gamma, gamma_dt, K,
-                                                                                   eps, bp, bc, kp);
+// Rows of a prompt: x = in + the splits of a product (added in split order; to
+// x_out, and to out_act in the act dtype); then RMSNorm(x) * gamma as the
+// prepared input of the next product, row r as row r mod 64 of block r / 64.
+// One wave per row, eight rows per workgroup (the eight 16-byte pieces a 128-byte
+// line of a block takes come from one workgroup), eight consecutive k per lane
+// and step; the row stays in registers up to 512 NS values (NS = 0: it is read
+// again, for longer rows).
+template <int NS>
+__global__ __launch_bounds__(512) void bprep_rows_kernel(PfRows a) {
+    const int lane = threadIdx.x & 63, r = 8 * blockIdx.x + (threadIdx.x >> 6);
+    if (r >= a.n) return;                                      // waves are independent: no barrier below
+    const int K = a.K;
+    auto load = [&](int k, float (&v)[8]) {
+        load8(a.in, a.in_dt, (size_t)r * a.in_ld + k, v);
+        for (int s = 0; s < a.nsplit; ++s) {
+            float p[8];
+            load8(a.part, DT_F32, (size_t)s * a.part_stride + (size_t)r * K + k, p);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] += p[e];
+        }
+    };
+    auto put_x = [&](int k, const float (&v)[8]) {
+        if (a.x_out) __builtin_memcpy(a.x_out + (size_t)r * K + k, v, 32);
+        if (a.out_act) {
+            uint16_t h[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) h[e] = to_half_bits(v[e], a.out_act_dt);
+            __builtin_memcpy((uint16_t*)a.out_act + (size_t)r * K + k, h, 16);
+        }
+    };
+    float x[NS ? NS : 1][8];
+    float ss = 0.f;
+    if constexpr (NS > 0) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int k = 512 * s + 8 * lane;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[s][e] = 0.f;
+            if (k < K) load8(a.in, a.in_dt, (size_t)r * a.in_ld + k, x[s]);
+        }
+        for (int sp = 0; sp < a.nsplit; ++sp) {
+            const float* pr = a.part + (size_t)sp * a.part_stride + (size_t)r * K + 8 * lane;
+#pragma unroll
+            for (int h = 0; h < NS; h += 8) {                  // eight steps' loads at once
+                float p[8][8];
+#pragma unroll
+                for (int s = 0; s < 8; ++s)
+                    if (512 * (h + s) + 8 * lane < K) load8(pr, DT_F32, 512 * (h + s), p[s]);
+#pragma unroll
+                for (int s = 0; s < 8; ++s)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        if (512 * (h + s) + 8 * lane < K) x[h + s][e] += p[s][e];
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int k = 512 * s + 8 * lane;
+            if (k < K) put_x(k, x[s]);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) ss += x[s][e] * x[s][e];
+        }
+    } else {
+        for (int k = 8 * lane; k < K; k += 512) {
+            load(k, x[0]);
+            put_x(k, x[0]);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) ss += x[0][e] * x[0][e];
+        }
+    }
+    if (!a.bp) return;
+    const float rs = rsqrtf(wave_sum_all(ss) / (float)K + a.eps);
+    uint16_t* bp = a.bp + (size_t)(r >> 6) * 64 * a.kp;
+    float* bc = a.bc + (size_t)(r >> 6) * 2 * a.kp;
+    auto prep = [&](int k, const float (&v)[8]) {
+        const bool in = k < K;
+        float g[8];
+        load8(a.gamma, a.gamma_dt, min(k, K - 8), g);
+        uint16_t c[8];
+        float cs = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float h16 = f16_to_f32(f32_to_f16(v[e] * rs * g[e]));
+            cs += bp_corr(h16, e);
+            c[e] = bp_code(h16, e);
+        }
+        cs = in ? cs : 0.f;
+        cs += dpp_f<0xB1>(cs);
+        cs += dpp_f<0x4E>(cs);                                 // the 4 lanes of 32 k
+        if (in) {
+            __builtin_memcpy(__builtin_assume_aligned(bp + bp_index(r & 63, k), 16), c, 16);
+            if ((k & 31) == 0) bc[bc_index(r & 63, k)] = cs;
+        }
+    };
+    if constexpr (NS > 0) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            if (512 * s < K) prep(512 * s + 8 * lane, x[s]);   // whole waves take part in the sums
+    } else {
+        for (int k0 = 0; k0 < K; k0 += 512) {
+            const int k = k0 + 8 * lane, kc = min(k, K - 8);
+            if (a.x_out) load8(a.x_out, DT_F32, (size_t)r * K + kc, x[0]);
+            else load(kc, x[0]);
+            prep(k, x[0]);
+        }
+    }
+}
+
+hipError_t launch_bprep_rows(const PfRows& a, hipStream_t st) {
+    if (a.K < 8 || a.K % 8 || a.n < 1 || (a.bp && (a.kp < a.K || a.kp % 128))) return hipErrorInvalidValue;
+    const dim3 grid((a.n + 7) / 8), block(512);
+    if (a.K <= 4096) bprep_rows_kernel<8><<<grid, block, 0, st>>>(a);
+    else if (a.K <= 8192) bprep_rows_kernel<16><<<grid, block, 0, st>>>(a);
+    else bprep_rows_kernel<0><<<grid, block, 0, st>>>(a);
     return hipGetLastError();
 }
 
@@ -1009,10 +1095,12 @@ __global__ __launch_bounds__(256, 2) void gemm_pf_kernel(PfArgs a) {
     // workgroups of one XCD (blockIdx mod 8) walk the tiles in bands of PF_BAND
     // token blocks: the 64 that run at once share 8 weight tile groups and 8
     // token blocks in the XCD's L2
-    const int total = a.nwt * a.ntb;
+    const int tiles = a.nwt * a.ntb, total = tiles * a.ksplit;
     const int per_xcd = (total + 7) / 8;
-    const int q = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    int q = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
     if ((int)(blockIdx.x >> 3) >= per_xcd || q >= total) return;   // whole workgroup: no barrier is reached
+    const int s = q / tiles;                                   // split of K
+    q -= s * tiles;
     const int band = q / (PF_BAND * a.nwt), inb = q - band * PF_BAND * a.nwt;
     const int bw = min(PF_BAND, a.ntb - band * PF_BAND);
     const int wt = inb / bw, tb = band * PF_BAND + inb % bw;
@@ -1021,7 +1109,7 @@ __global__ __launch_bounds__(256, 2) void gemm_pf_kernel(PfArgs a) {
     const bool has = t < W.ntiles;
     const int tt = has ? t : W.ntiles - 1;                     // loads stay in bounds; results are dropped
     const int K = W.k;
-    const int ng = (K + 127) / 128;
+    const int g0 = s * a.kg, ng = min((K + 127) / 128, g0 + a.kg);   // this split's groups: g0 .. ng - 1
     // buffer resources: uniform group offsets, one 32-bit offset per lane
     const __amdgpu_buffer_rsrc_t rbp = attn_rsrc(a.bp + (size_t)tb * a.bp_blk, (uint32_t)a.bp_blk * 2);
     const __amdgpu_buffer_rsrc_t rbc = attn_rsrc(a.bc + (size_t)tb * a.bc_blk, (uint32_t)a.bc_blk * 4);
@@ -1085,23 +1173,23 @@ __global__ __launch_bounds__(256, 2) void gemm_pf_kernel(PfArgs a) {
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) acc[rt][cb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-    ld_b(0);
+    ld_b(g0);
 #pragma unroll
-    for (int rt = 0; rt < 4; ++rt) ld_w(0, rt);
-    st_b(0);
-    ld_b(min(1, ng - 1));
+    for (int rt = 0; rt < 4; ++rt) ld_w(g0, rt);
+    st_b(g0);
+    ld_b(min(g0 + 1, ng - 1));
     __syncthreads();
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) A[cb][i] = __builtin_bit_cast(half8_t, sb[0][4 * cb + i][lane]);
-        c[0][cb] = *(const f32x4_t*)&sc[0][16 * cb + 4 * lg];
+        for (int i = 0; i < 4; ++i) A[cb][i] = __builtin_bit_cast(half8_t, sb[g0 & 1][4 * cb + i][lane]);
+        c[0][cb] = *(const f32x4_t*)&sc[g0 & 1][16 * cb + 4 * lg];
         c[1][cb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
     decode(cw[0], B[0]);
     scl[0] = f16_to_f32(cs[0]);
     scl[1] = 0.f;
-    ld_w(min(1, ng - 1), 0);
+    ld_w(min(g0 + 1, ng - 1), 0);
     // One group in four steps of one 16-row weight block: 16 products, k slice by
     // k slice over four independent token blocks.  While a step's products run, the
     // step before's results are scaled into the sums and its registers reloaded with
@@ -1111,7 +1199,7 @@ __global__ __launch_bounds__(256, 2) void gemm_pf_kernel(PfArgs a) {
     // operands and corrections), and step 3 replaces each token operand after its
     // last product.  Past the last group the loads repeat it and what they feed is
     // not used.
-    for (int g = 0; g < ng; ++g) {
+    for (int g = g0; g < ng; ++g) {
         const int buf = g & 1, gn = min(g + 1, ng - 1);
 #pragma unroll
         for (int rt = 0; rt < 4; ++rt) {
@@ -1150,25 +1238,40 @@ __global__ __launch_bounds__(256, 2) void gemm_pf_kernel(PfArgs a) {
     for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[3][cb][j] = __builtin_fmaf(scl[1], c[1][cb][j], acc[3][cb][j]);
-    if (!has) return;
-
     // ---- epilogue: lane holds row 64 t + 16 rt + l16 of tokens 64 tb + 16 cb + 4 lg + j
-    if (a.epi == EPI_SWIGLU) {                                 // rows 0..31 of a tile gate, 32..63 the matching up
+    if (a.epi == EPI_SWIGLU) {
+        // rows 0..31 of a tile gate, 32..63 the matching up: the workgroup's four
+        // tiles give one whole group of 128 values of the down product's input,
+        // written in prepared form (wave w: chunk w) through LDS as 16 KB in a row.
+        // Values past n_valid are zero.
+        __syncthreads();                                        // the operands in sb are no longer read
+        uint16_t* sy = (uint16_t*)&sb[0][0][0];
+        float* bco = a.bc_out + (size_t)tb * a.out_bc_blk + (size_t)wt * 256 + w;
 #pragma unroll
-        for (int rt = 0; rt < 2; ++rt)
+        for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
-            for (int cb = 0; cb < 4; ++cb)
+            for (int j = 0; j < 4; ++j) {
+                const int m = 16 * cb + 4 * lg + j;
+                float cs = 0.f;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int tok = 64 * tb + 16 * cb + 4 * lg + j;
+                for (int rt = 0; rt < 2; ++rt) {
                     const int f = 32 * t + 16 * rt + l16;
-                    if (tok < a.n && f < a.n_valid) {
-                        const float gt = acc[rt][cb][j], up = acc[rt + 2][cb][j];
-                        a.out[(size_t)tok * a.out_ld + f] = (gt / (1.0f + expf(-gt))) * up;
-                    }
+                    const float gt = acc[rt][cb][j], up = acc[rt + 2][cb][j];
+                    const float y = has && f < a.n_valid ? (gt / (1.0f + expf(-gt))) * up : 0.f;
+                    const float h16 = f16_to_f32(f32_to_f16(y));
+                    cs += bp_corr(h16, l16);
+                    sy[((4 * cb + 2 * rt + (l16 >> 3)) * 64 + 16 * w + 4 * lg + j) * 8 + (l16 & 7)] = bp_code(h16, l16);
                 }
+                cs = sum16(cs);
+                if (l16 == 0) bco[4 * m] = cs;
+            }
+        __syncthreads();
+        u32x4* bpo = (u32x4*)(a.bp_out + (size_t)tb * a.out_bp_blk) + (size_t)wt * 1024 + tid;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) bpo[256 * u] = (&sb[0][0][0])[tid + 256 * u];
         return;
     }
+    if (!has) return;
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
@@ -1180,6 +1283,10 @@ __global__ __launch_bounds__(256, 2) void gemm_pf_kernel(PfArgs a) {
                 const int row = 64 * t + 16 * rt + l16;
                 if (row >= W.n) continue;
                 float v = acc[rt][cb][j];
+                if (a.ksplit > 1) {                            // this split's sums; the next bprep_rows_kernel adds them
+                    a.part[(size_t)s * a.part_stride + (size_t)tok * a.out_ld + row] = v;
+                    continue;
+                }
                 if (a.epi == EPI_RESID) {
                     v += load_val(a.resid, a.resid_dt, (size_t)tok * a.resid_ld + row);
                     if (a.out_act) ((uint16_t*)a.out_act)[(size_t)tok * a.out_act_ld + row] = to_half_bits(v, a.out_act_dt);
@@ -1191,7 +1298,10 @@ __global__ __launch_bounds__(256, 2) void gemm_pf_kernel(PfArgs a) {
 
 hipError_t launch_gemm_pf(const PfArgs& a, hipStream_t st) {
     if (a.n < 1 || a.W.gchunks != 4 || a.nwt != (a.W.ntiles + 3) / 4 || a.ntb != (a.n + 63) / 64) return hipErrorInvalidValue;
-    const int total = a.nwt * a.ntb;
+    const int ng = (a.W.k + 127) / 128;                        // every split holds at least one group
+    if (a.ksplit < 1 || a.kg < 1 || a.ksplit * a.kg < ng || (a.ksplit - 1) * a.kg >= ng) return hipErrorInvalidValue;
+    if (a.ksplit > 1 && (!a.part || a.epi != EPI_RESID)) return hipErrorInvalidValue;
+    const int total = a.nwt * a.ntb * a.ksplit;
     const unsigned grid = 8u * (unsigned)((total + 7) / 8);
     if (a.W.k % 128) gemm_pf_kernel<true><<<dim3(grid), dim3(256), 0, st>>>(a);
     else gemm_pf_kernel<false><<<dim3(grid), dim3(256), 0, st>>>(a);

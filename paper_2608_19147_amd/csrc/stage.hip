@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <array>
+#include <climits>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -80,6 +81,25 @@ void bp_plan(DevMat& m) {
     m.bp_kg = kg;
 }
 
+// K split of a prompt's residual product (o, down) over `tiles` workgroup tiles
+// of `ng` groups: the split that leaves the fullest CU the least work, a start
+// and an end counted as PF_SPLIT_COST groups; at most 8, at least 8 groups each.
+constexpr int PF_SPLIT_COST = 6;
+void pf_plan(int tiles, int ng, int n_cus, int& splits, int& kg) {
+    int best = INT_MAX;
+    splits = 1;
+    kg = ng;
+    for (int S = 1; S <= 8 && ng >= 8 * S; ++S) {
+        const int per = (ng + S - 1) / S, used = (ng + per - 1) / per;
+        const int cost = (tiles * used + n_cus - 1) / n_cus * (per + PF_SPLIT_COST);
+        if (cost < best) {
+            best = cost;
+            splits = used;
+            kg = per;
+        }
+    }
+}
+
 struct LayerDev {
     DevMat qkv, o, gu, d;
     uint16_t* attn_norm = nullptr;
@@ -127,9 +147,11 @@ struct Stage {
     int embed_vocab = 0;
     unsigned* embed_err = nullptr;                     // set by a gather that met an id outside the table
     // prefill workspace for pf_rows prompt rows: residual fp32 [rows][H], q|k|v fp32
-    // [rows][NQKV], SwiGLU output fp32 [rows][F], prepared inputs (64-row blocks)
-    float *pf_x = nullptr, *pf_qkv = nullptr, *pf_act = nullptr, *pf_bc = nullptr;
-    uint16_t* pf_bp = nullptr;
+    // [rows][NQKV], attention output fp32 [rows][Hq*D], prepared inputs (64-row
+    // blocks; [1]: the down product's)
+    float *pf_x = nullptr, *pf_qkv = nullptr, *pf_attn = nullptr, *pf_bc[2] = {nullptr, nullptr};
+    uint16_t* pf_bp[2] = {nullptr, nullptr};
+    float* pf_part = nullptr;                          // sums of the split residual products [splits][rows][H]
     size_t pf_rows = 0;
     // persistent-kernel weights (row layout) and barrier state
     bool ps_ok = false;
@@ -164,12 +186,14 @@ struct Stage {
     hipStream_t last_stream = nullptr;
     bool done_used = false;
 
+    std::array<void*, 8> pf_buffers() const { return {pf_x, pf_qkv, pf_attn, pf_bp[0], pf_bp[1], pf_bc[0], pf_bc[1], pf_part}; }
+
     ~Stage() {
         for (hipEvent_t e : prof_ev) (void)hipEventDestroy(e);
         if (pf_x) {
             (void)hipSetDevice(device);
             (void)hipDeviceSynchronize();
-            for (void* p : {(void*)pf_x, (void*)pf_qkv, (void*)pf_act, (void*)pf_bc, (void*)pf_bp}) (void)hipFree(p);
+            for (void* p : pf_buffers()) (void)hipFree(p);
         }
         if (done_ev) (void)hipEventDestroy(done_ev);
         (void)hipSetDevice(device);
@@ -1334,15 +1358,26 @@ int stage_prefill(Stage* st, KVState* kv, int n, const int32_t* positions, const
     const size_t wrows = (size_t)(pass_rows + 63) / 64 * 64;
     if (st->pf_rows < wrows) {
         HIP_TRY(hipDeviceSynchronize());
-        for (void* p : {(void*)st->pf_x, (void*)st->pf_qkv, (void*)st->pf_act, (void*)st->pf_bc, (void*)st->pf_bp})
+        for (void* p : st->pf_buffers())
             if (p) HIP_TRY(hipFree(p));
-        st->pf_x = st->pf_qkv = st->pf_act = st->pf_bc = nullptr;
-        st->pf_bp = nullptr;
+        st->pf_x = st->pf_qkv = st->pf_attn = st->pf_bc[0] = st->pf_bc[1] = nullptr;
+        st->pf_bp[0] = st->pf_bp[1] = nullptr;
+        st->pf_part = nullptr;
         st->pf_rows = 0;
+        size_t prows = 0;                              // rows of split sums: the most that any prompt of at most wrows rows takes
+        for (int nb = 1; nb <= (int)(wrows / 64); ++nb)
+            for (const DevMat* m : {&st->layers[0].o, &st->layers[0].d}) {
+                int S, kg;
+                pf_plan((m->pm.ntiles + 3) / 4 * nb, (m->pm.k + 127) / 128, st->n_cus, S, kg);
+                if (S > 1) prows = std::max(prows, (size_t)S * nb * 64);
+            }
+        const size_t kin = (size_t)(std::max(H, Hq * D) + 127) / 128 * 128, kf = (size_t)(F + 127) / 128 * 128;
         if (hipMalloc(&st->pf_x, wrows * H * 4) != hipSuccess || hipMalloc(&st->pf_qkv, wrows * nqkv * 4) != hipSuccess ||
-            hipMalloc(&st->pf_act, wrows * std::max(F, Hq * D) * 4) != hipSuccess ||
-            hipMalloc(&st->pf_bp, wrows * st->kp * 2) != hipSuccess ||
-            hipMalloc(&st->pf_bc, wrows / 64 * 2 * st->kp * 4) != hipSuccess) {
+            hipMalloc(&st->pf_attn, wrows * Hq * D * 4) != hipSuccess ||
+            hipMalloc(&st->pf_bp[0], wrows * kin * 2) != hipSuccess || hipMalloc(&st->pf_bp[1], wrows * kf * 2) != hipSuccess ||
+            hipMalloc(&st->pf_bc[0], wrows / 64 * 2 * kin * 4) != hipSuccess ||
+            hipMalloc(&st->pf_bc[1], wrows / 64 * 2 * kf * 4) != hipSuccess ||
+            (prows && hipMalloc(&st->pf_part, prows * H * 4) != hipSuccess)) {
             (void)hipGetLastError();
             return fail(STAGE_E_OOM, "prefill workspace allocation failed");
         }
@@ -1415,20 +1450,59 @@ int stage_prefill(Stage* st, KVState* kv, int n, const int32_t* positions, const
     // ---------------- passes of at most PF_ROWS rows, each through every layer: the
     // products take all of a pass's rows at once (gemm_pf_kernel), the attention
     // one 64-row chunk at a time (its keys include the earlier chunks' rows)
-    const int kp = st->kp;
-    const size_t bp_blk = (size_t)64 * kp, bc_blk = (size_t)2 * kp;
+    const int kin = (std::max(H, Hq * D) + 127) / 128 * 128, kf = (F + 127) / 128 * 128;   // k of the two prepared inputs
     auto pf = [&](const DevMat& mat, int rows, int epi) {
         PfArgs a{};
         a.W = mat.pm;
-        a.bp = st->pf_bp;
-        a.bc = st->pf_bc;
-        a.bp_blk = bp_blk;
-        a.bc_blk = bc_blk;
+        a.bp = st->pf_bp[0];
+        a.bc = st->pf_bc[0];
+        a.bp_blk = (size_t)64 * kin;
+        a.bc_blk = (size_t)2 * kin;
         a.n = rows;
         a.epi = epi;
         a.nwt = (mat.pm.ntiles + 3) / 4;
         a.ntb = (rows + 63) / 64;
+        a.ksplit = 1;
+        a.kg = (mat.pm.k + 127) / 128;
         return a;
+    };
+    // a residual product whose tiles leave CUs idle is split over K; its sums are
+    // added to the residual by the next rows() call
+    int pending = 0;
+    const void* pend_in = nullptr;
+    int pend_dt = DT_F32;
+    auto run_resid = [&](PfArgs& a) -> hipError_t {
+        pf_plan(a.nwt * a.ntb, a.kg, st->n_cus, a.ksplit, a.kg);
+        pending = a.ksplit > 1 ? a.ksplit : 0;
+        pend_in = a.resid;
+        pend_dt = a.resid_dt;
+        a.part = st->pf_part;
+        a.part_stride = (size_t)a.n * H;
+        return launch_gemm_pf(a, s);
+    };
+    // rows between two products: pending sums into pf_x, then the next product's
+    // input with the norm weight gamma (null: the last layer's output only)
+    auto rows = [&](const void* in, int in_dt, int n_rows, const uint16_t* gamma, void* out_act) -> hipError_t {
+        PfRows a{};
+        a.in = pending ? pend_in : in;
+        a.in_dt = pending ? pend_dt : in_dt;
+        a.in_ld = H;
+        a.part = st->pf_part;
+        a.nsplit = pending;
+        a.part_stride = (size_t)n_rows * H;
+        a.x_out = pending && gamma ? st->pf_x : nullptr;
+        a.out_act = out_act;
+        a.out_act_dt = act_dt;
+        a.gamma = gamma;
+        a.gamma_dt = act_dt;
+        a.K = H;
+        a.eps = c.rms_eps;
+        a.n = n_rows;
+        a.bp = gamma ? st->pf_bp[0] : nullptr;
+        a.bc = st->pf_bc[0];
+        a.kp = kin;
+        pending = 0;
+        return launch_bprep_rows(a, s);
     };
     for (int p0 = 0; p0 < n; p0 += PF_ROWS) {
         const int pr = std::min(PF_ROWS, n - p0);
@@ -1438,8 +1512,7 @@ int stage_prefill(Stage* st, KVState* kv, int n, const int32_t* positions, const
             const bool first = (l == 0), last = (l == c.n_layers - 1);
             // q|k|v = RMSNorm(x) W_qkv^T
             HIP_TRY(prof_mark(st, STAGE_KERNEL_QKV, true, s));
-            HIP_TRY(launch_bprep_rows(first ? (const void*)hin : (const void*)st->pf_x, first ? act_dt : DT_F32, H,
-                                      Ld.attn_norm, act_dt, H, c.rms_eps, pr, st->pf_bp, st->pf_bc, kp, s));
+            HIP_TRY(rows(first ? (const void*)hin : (const void*)st->pf_x, first ? act_dt : DT_F32, pr, Ld.attn_norm, nullptr));
             {
                 PfArgs a = pf(Ld.qkv, pr, EPI_STORE);
                 a.out = st->pf_qkv;
@@ -1460,7 +1533,7 @@ int stage_prefill(Stage* st, KVState* kv, int n, const int32_t* positions, const
                 AttnArgs a{};
                 a.qkv = st->pf_qkv;
                 a.qkv_ld = nqkv;
-                a.out = st->pf_act;                                  // scratch: the gate|up product rewrites it
+                a.out = st->pf_attn;
                 a.out_ld = Hq * D;
                 a.meta.reqs = (const ReqDev*)(db + off_req) + q0;
                 a.meta.items = (const ItemDev*)(db + off_item) + q0;
@@ -1486,9 +1559,9 @@ int stage_prefill(Stage* st, KVState* kv, int n, const int32_t* positions, const
                     sl = (sl + KGROUPS - 1) / KGROUPS * KGROUPS;
                     a.dma = st->attn_dma && sl <= 1024 && lstride * 2 <= 0xFFFFFFF0ull ? 1 : 0;
                 }
-                a.bp_out = st->pf_bp;
-                a.bc_out = st->pf_bc;
-                a.kp = kp;
+                a.bp_out = st->pf_bp[0];
+                a.bc_out = st->pf_bc[0];
+                a.kp = kin;
                 a.no_append = 1;
                 HIP_TRY(launch_attention(a, D, (Hq / Hkv) * PF_ATT_ROWS, s));
             }
@@ -1502,25 +1575,30 @@ int stage_prefill(Stage* st, KVState* kv, int n, const int32_t* positions, const
                 a.resid = first ? (const void*)hin : (const void*)st->pf_x;
                 a.resid_dt = first ? act_dt : DT_F32;
                 a.resid_ld = H;
-                HIP_TRY(launch_gemm_pf(a, s));
+                HIP_TRY(run_resid(a));
             }
             HIP_TRY(prof_mark(st, STAGE_KERNEL_OPROJ, false, s));
             // act = silu(h2 W_g^T) * (h2 W_u^T), h2 = RMSNorm(x)
             HIP_TRY(prof_mark(st, STAGE_KERNEL_GATEUP, true, s));
-            HIP_TRY(launch_bprep_rows(st->pf_x, DT_F32, H, Ld.ffn_norm, act_dt, H, c.rms_eps, pr, st->pf_bp, st->pf_bc, kp, s));
+            HIP_TRY(rows(st->pf_x, DT_F32, pr, Ld.ffn_norm, nullptr));
             {
                 PfArgs a = pf(Ld.gu, pr, EPI_SWIGLU);
-                a.out = st->pf_act;
-                a.out_ld = F;
+                a.bp_out = st->pf_bp[1];
+                a.bc_out = st->pf_bc[1];
+                a.out_bp_blk = (size_t)64 * kf;
+                a.out_bc_blk = (size_t)2 * kf;
                 a.n_valid = F;
                 HIP_TRY(launch_gemm_pf(a, s));
             }
             HIP_TRY(prof_mark(st, STAGE_KERNEL_GATEUP, false, s));
             // x = x + act W_d^T; the last layer also writes hidden_out
             HIP_TRY(prof_mark(st, STAGE_KERNEL_DOWN, true, s));
-            HIP_TRY(launch_bprep_rows(st->pf_act, DT_F32, F, nullptr, act_dt, F, c.rms_eps, pr, st->pf_bp, st->pf_bc, kp, s));
             {
                 PfArgs a = pf(Ld.d, pr, EPI_RESID);
+                a.bp = st->pf_bp[1];
+                a.bc = st->pf_bc[1];
+                a.bp_blk = (size_t)64 * kf;
+                a.bc_blk = (size_t)2 * kf;
                 a.out = st->pf_x;
                 a.out_ld = H;
                 a.resid = st->pf_x;
@@ -1531,7 +1609,8 @@ int stage_prefill(Stage* st, KVState* kv, int n, const int32_t* positions, const
                     a.out_act_dt = act_dt;
                     a.out_act_ld = H;
                 }
-                HIP_TRY(launch_gemm_pf(a, s));
+                HIP_TRY(run_resid(a));
+                if (last && pending) HIP_TRY(rows(nullptr, DT_F32, pr, nullptr, a.out_act));
             }
             HIP_TRY(prof_mark(st, STAGE_KERNEL_DOWN, false, s));
         }

@@ -130,13 +130,25 @@ struct AttnArgs {
     int nsplit_max;
     int vector_path;         // 1: attn_kernel (vector units) instead of attn_mma_kernel
     uint16_t* bp_out; float* bc_out; int kp;   // the attention output also in prepared form (o product input, 64-row blocks)
-    int no_append;           // the rows of this forward are already in the cache (prefill): do not write them
     int dma;                 // 1: cache rows by direct loads (attn_dma_kernel) where the launch allows it: every
                              // split at most 1024 keys, per-row masks of at most 8 KB per split, at most 256
                              // query vectors per kv head
     // test support (null unless armed): the rotated queries [M][Hq][D] and the
     // scores q.k / sqrt(D) of every visible key [M][Hq][dbg_keys]
     float* dbg_q; float* dbg_logits; int dbg_keys;
+};
+
+// Prefill attention (attn_pf_kernel): n prompt rows of a one-slot state, whose
+// own rows and the P before them are in the cache.
+struct PfAttnArgs {
+    const float* qkv; int qkv_ld;
+    const int* pos;                                // [n] rotary positions
+    const float2* rope;
+    const uint16_t *kl, *vl; int cap;              // this layer's [Hkv][cap][D]
+    int P, n, Hq, Hkv, kv_dt;
+    const uint32_t* mask;                          // null, or one bit per cache row (1: kept), 32 rows a word
+    float qscale;                                  // log2(e) / sqrt(D)
+    uint16_t* bp; float* bc; int kp;               // the o product's input, 64-row blocks
 };
 
 // ---- single-launch stage forward (persistent.hip)
@@ -288,6 +300,7 @@ hipError_t launch_bprep(const void* in, int in_dt, int in_ld, const uint16_t* ga
                         int M, uint16_t* bp, float* bc, int kp, float* rs_out, hipStream_t st);
 // queries_per_item_max: the largest (rows of an item) x (query heads per kv head).
 hipError_t launch_attention(const AttnArgs& a, int head_dim, int queries_per_item_max, hipStream_t st);
+hipError_t launch_attention_pf(const PfAttnArgs& a, int head_dim, int n_cus, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t st);
 hipError_t launch_table_gather(const int16_t* src, int16_t* dst, const int* beam, int S, int cap, int P, hipStream_t st);
 hipError_t launch_kv_append(uint16_t* kc, uint16_t* vc, int16_t* table, const uint16_t* k, const uint16_t* v,

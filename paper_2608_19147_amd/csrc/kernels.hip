@@ -1483,7 +1483,7 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
             }
             consume(j, kf, vf);
         }
-        if (r0 == 0 && !a.no_append) {                          // append: owner of row j writes it
+        if (r0 == 0) {                          // append: owner of row j writes it
             for (int j = max(j0, P) + kg; j < j1; j += KGROUPS) {
                 const int i = j - P;
                 const int m = rowbase + i;
@@ -1778,7 +1778,7 @@ __global__ __launch_bounds__(256, QTW == 1 ? 2 : 1) void attn_mma_kernel(AttnArg
         stab[tid + 256 * t2] = ptab[t2];
     }
     __syncthreads();
-    fetch(0, !a.no_append);
+    fetch(0, true);
     for (int qg = 0; qg < nqt; qg += 4 * QTW) {
         // ---- this wave's query tiles: rotated, scaled, split into rounded part and residual
         u32x4 qh[QTW][DB], qr[QTW][DB];
@@ -1864,14 +1864,14 @@ __global__ __launch_bounds__(256, QTW == 1 ? 2 : 1) void attn_mma_kernel(AttnArg
                 stab[x] = j < P ? tab[j] : (int16_t)b;
             }
             __syncthreads();
-            fetch(0, qg == 0 && !a.no_append);
+            fetch(0, qg == 0);
         }
         const int nsteps = (c1 - c0 + AK - 1) / AK;
         stash(0);
         __syncthreads();
         for (int st = 0; st < nsteps; ++st) {
             const int buf = st & 1;
-            if (st + 1 < nsteps) fetch((st + 1) * AK, qg == 0 && !a.no_append);   // next step's loads fly during this one
+            if (st + 1 < nsteps) fetch((st + 1) * AK, qg == 0);   // next step's loads fly during this one
             // the lane's 8 keys: step key 4 lg + e (e < 4) or 16 + 4 lg + e - 4; visible ones as bits
             const int kbase = c0 + st * AK + 4 * lg;
             uint32_t vbits = 0u;
@@ -2264,12 +2264,11 @@ __global__ __launch_bounds__(256, QTW == 1 ? 2 : 1) void attn_dma_kernel(AttnArg
                     kk[w2] = (uint32_t)kb8[2 * w2] | ((uint32_t)kb8[2 * w2 + 1] << 16);
                     vv[w2] = (uint32_t)vb8[2 * w2] | ((uint32_t)vb8[2 * w2 + 1] << 16);
                 }
-                if (!a.no_append) {                          // append: owner of row j writes it
-                    const size_t off = (((size_t)b * Hkv + g) * rq.cap + j) * D + 8 * c;
-                    *(u32x4*)(kl + off) = kk;
-                    *(u32x4*)(vl + off) = vv;
-                    if (a.layer == 0 && g == 0 && c == 0) rq.table[(size_t)b * rq.cap + j] = (int16_t)b;
-                }
+                // append: owner of row j writes it
+                const size_t off = (((size_t)b * Hkv + g) * rq.cap + j) * D + 8 * c;
+                *(u32x4*)(kl + off) = kk;
+                *(u32x4*)(vl + off) = vv;
+                if (a.layer == 0 && g == 0 && c == 0) rq.table[(size_t)b * rq.cap + j] = (int16_t)b;
                 if (smk[x0 + k] != 0) {                      // a kept row enters; a dropped one stays zero
                     const int pos16 = 16 * (c ^ (k % NCH));
                     *(u32x4*)(kb + k * RB + pos16) = kk;
@@ -2466,6 +2465,289 @@ hipError_t launch_attention(const AttnArgs& a, int head_dim, int queries_per_ite
 #undef ATTN_MMA
 #undef ATTN_MMA_R
 #undef ATTN_DMA_Q
+    return hipGetLastError();
+}
+
+// ------------------------------------------------------------------ prefill attention
+//
+// Causal attention of a prompt's rows (already in the cache) and the rows before
+// them, for one layer of a one-slot state: cache rows are read where they lie,
+// no beam table.  A workgroup takes 64 QTW consecutive query vectors (token i,
+// head of the group) of one kv head and every key they see, so the result leaves
+// it finished and normalized, as the o product's prepared input: no partials, no
+// merge launch.  Eight waves: four query tiles (times QTW) by two key groups,
+// which take alternate 32-key steps and are merged through LDS at the end.
+// Scores, softmax and output as attn_dma_kernel (query as two cache-dtype terms,
+// S^T = K Q^T, O^T += V^T P^T).  Each step's rows go through registers into one
+// of two LDS buffers per group while the step before computes; a wave reads the
+// step's K and V once for its QTW query tiles, and with one tile the LDS reads
+// (1024 cycles for the eight waves' steps) take longer than the products (768),
+// so QTW = 2 where the prompt has workgroups enough.
+// Masked rows and rows past the block's last query enter as zeros with a -inf score.
+template <int D, int KVDT, int QTW>
+__global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
+    constexpr int HALF = D / 2, NCH = D / 8, DB = D / 32, MB = D / 16, RB = 2 * D;
+    constexpr int SB = AK * RB;                              // bytes of one step's K (or V)
+    constexpr int NL = SB / 16 / 256;                        // 16-byte pieces per thread and step, K and V each
+    static_assert(NL >= 1, "step geometry");
+    __shared__ __attribute__((aligned(16))) uint8_t kv[2][2][2][SB];   // [key group][buffer][K, V]
+    __shared__ float2 sml[4 * QTW][64];
+    static_assert(sizeof(kv) >= (size_t)4 * QTW * MB * 1024, "merge staging");
+    const int g = blockIdx.x % a.Hkv, blk = gridDim.x / a.Hkv - 1 - blockIdx.x / a.Hkv;   // longest first
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kg = wave >> 2, qw = wave & 3, tg = tid & 255;
+    const int ql = lane & 15, lg = lane >> 4;
+    const int Hq = a.Hq, gs = Hq / a.Hkv;
+    const int R = a.n * gs, r0 = blk * 64 * QTW;
+    const int kend = a.P + (min(R, r0 + 64 * QTW) - 1) / gs + 1;   // keys the block's last query sees
+    const int nsteps = (kend + AK - 1) / AK;
+    const uint16_t* kh = a.kl + (size_t)g * a.cap * D;
+    const uint16_t* vh = a.vl + (size_t)g * a.cap * D;
+
+    // ---- step st of this key group: its pieces to registers, then (masked rows as
+    // zeros) to LDS; piece u of thread tg is chunk (tg + 256 u) mod NCH of its key,
+    // stored at that chunk ^ (key mod NCH)
+    u32x4 rk[NL], rv[NL];
+    uint32_t word = 0u;                                      // key mask of the step held in rk, rv
+    auto ld = [&](int st) {
+        const uint32_t bytes = (uint32_t)max(0, min(AK, kend - AK * st)) * RB;   // later rows read as zeros
+        const size_t base = (size_t)min(st, nsteps - 1) * AK * D;
+        const __amdgpu_buffer_rsrc_t bk = attn_rsrc(kh + base, bytes), bv = attn_rsrc(vh + base, bytes);
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            rk[u] = pf_load16(bk, 16u * tg, 4096u * u);
+            rv[u] = pf_load16(bv, 16u * tg, 4096u * u);
+        }
+        word = a.mask ? a.mask[min(st, nsteps - 1)] : ~0u;
+    };
+    auto put = [&](int buf) {
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            const int idx = tg + 256 * u, key = idx / NCH, c = idx % NCH;
+            u32x4 k = rk[u], v = rv[u];
+            if (word != ~0u) {
+                const bool in = (word >> key) & 1u;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    k[e] = in ? k[e] : 0u;
+                    v[e] = in ? v[e] : 0u;
+                }
+            }
+            const int at = key * RB + 16 * (c ^ (key % NCH));
+            *(u32x4*)&kv[kg][buf][0][at] = k;
+            *(u32x4*)&kv[kg][buf][1][at] = v;
+        }
+    };
+    ld(kg);
+
+    // ---- this wave's query tiles: rotated, scaled, split into rounded part and residual
+    u32x4 qh[QTW][DB], qr[QTW][DB];
+    int qtok[QTW];
+    float mrun[QTW], lsum[QTW];
+    f32x4_t o[QTW][MB];
+#pragma unroll
+    for (int u = 0; u < QTW; ++u) {
+        const int r = r0 + 16 * (qw + 4 * u) + ql;
+        const bool ok = r < R;
+        const int i = ok ? r / gs : a.n - 1, h = g * gs + (ok ? r % gs : 0);   // the last row stands in past the end
+        qtok[u] = i;
+        mrun[u] = -INFINITY;
+        lsum[u] = 0.f;
+        const float* qrow = a.qkv + (size_t)i * a.qkv_ld + (size_t)h * D;
+        const float2* rp = a.rope + (size_t)a.pos[i] * HALF;
+#pragma unroll
+        for (int ib = 0; ib < DB; ++ib) {
+            const int d0 = 32 * ib + 8 * lg;                 // dims d0 .. d0 + 7 lie in one rotary half
+            const bool lo_half = d0 < HALF;
+            float x[8], xp[8];
+            float2 cs[8];
+            __builtin_memcpy(x, qrow + d0, 32);
+            __builtin_memcpy(xp, qrow + (lo_half ? d0 + HALF : d0 - HALF), 32);
+            __builtin_memcpy(cs, rp + (lo_half ? d0 : d0 - HALF), 64);
+            uint16_t hb[8], rb[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float y = (lo_half ? (x[e] * cs[e].x - xp[e] * cs[e].y) : (x[e] * cs[e].x + xp[e] * cs[e].y)) * a.qscale;
+                hb[e] = kv_round<KVDT>(y);
+                rb[e] = kv_round<KVDT>(y - kv_float<KVDT>(hb[e]));
+            }
+#pragma unroll
+            for (int w2 = 0; w2 < 4; ++w2) {
+                qh[u][ib][w2] = (uint32_t)hb[2 * w2] | ((uint32_t)hb[2 * w2 + 1] << 16);
+                qr[u][ib][w2] = (uint32_t)rb[2 * w2] | ((uint32_t)rb[2 * w2 + 1] << 16);
+            }
+        }
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) o[u][mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
+    const int tok0 = min(R - 1, r0 + 16 * qw) / gs;          // the wave's first token: steps up to it are causal for all
+
+    uint32_t cword = word;
+    put(0);
+    ld(kg + 2);
+    for (int st = kg, it = 0; st - kg < nsteps; st += 2, ++it) {   // the same number of turns in both groups
+        const int buf = it & 1;
+        __syncthreads();                                     // this buffer is complete; the other one is free
+        const uint32_t w0 = cword;                           // this step's key mask
+        cword = word;
+        put(buf ^ 1);
+        ld(st + 4);
+        if (st >= nsteps) continue;
+        const uint8_t* kb = kv[kg][buf][0];
+        const uint8_t* vb = kv[kg][buf][1];
+        u32x4 kf0[DB], kf1[DB], vf[MB];
+#pragma unroll
+        for (int ib = 0; ib < DB; ++ib) {
+            const int c = 4 * ib + lg;
+            kf0[ib] = *(const u32x4*)&kb[ql * RB + 16 * (c ^ (ql % NCH))];
+            kf1[ib] = *(const u32x4*)&kb[(16 + ql) * RB + 16 * (c ^ ((16 + ql) % NCH))];
+        }
+        // value fragments: read h gives keys 16 h + 4 lg + e; this lane supplies
+        // key 16 h + 4 lg + ql / 4, dims 16 mb + 4 (ql mod 4) .. + 3
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            typedef short s16x4 __attribute__((ext_vector_type(4)));
+            u32x2 p[2];
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh) {
+                const int key = 16 * hh + 4 * lg + (ql >> 2);
+                const int d = 16 * mb + 4 * (ql & 3);
+                const uint8_t* ad = vb + key * RB + 16 * ((d >> 3) ^ (key % NCH)) + 2 * (d & 7);
+                p[hh] = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                                      (__attribute__((address_space(3))) s16x4*)ad));
+            }
+            vf[mb] = u32x4{p[0][0], p[0][1], p[1][0], p[1][1]};
+        }
+        const bool all = w0 == ~0u && AK * st + AK - 1 <= a.P + tok0;   // every key of the step is seen by every query (uniform)
+        const int kbase = AK * st + 4 * lg;
+#pragma unroll
+        for (int u = 0; u < QTW; ++u) {
+            f32x4_t s0 = f32x4_t{0.f, 0.f, 0.f, 0.f}, s1 = s0;
+#pragma unroll
+            for (int ib = 0; ib < DB; ++ib) {
+                s0 = mma_kv<KVDT>(kf0[ib], qh[u][ib], s0);
+                s1 = mma_kv<KVDT>(kf1[ib], qh[u][ib], s1);
+                s0 = mma_kv<KVDT>(kf0[ib], qr[u][ib], s0);
+                s1 = mma_kv<KVDT>(kf1[ib], qr[u][ib], s1);
+            }
+            float sv[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) sv[e] = e < 4 ? s0[e] : s1[e - 4];
+            if (!all) {
+                const int last = a.P + qtok[u] - kbase;      // keys up to kbase + last are causal
+                const uint32_t vbits = w0 >> (4 * lg);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int ko = (e < 4) ? e : 12 + e;
+                    sv[e] = (((vbits >> ko) & 1u) && ko <= last) ? sv[e] : -INFINITY;
+                }
+            }
+            float mx = sv[0];
+#pragma unroll
+            for (int e = 1; e < 8; ++e) mx = fmaxf(mx, sv[e]);
+            float x0f, x1f;
+            lane_pair_k(mx, 16, x0f, x1f);
+            mx = fmaxf(x0f, x1f);
+            lane_pair_k(mx, 32, x0f, x1f);
+            mx = fmaxf(x0f, x1f);
+            const float mn = fmaxf(mrun[u], mx);
+            // no key seen yet (mn = -inf): base 0 makes every term and the correction 0
+            const float base = mn == -INFINITY ? 0.f : mn;
+            const float corr = __builtin_amdgcn_exp2f(mrun[u] - base);
+            float pv[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) pv[e] = __builtin_amdgcn_exp2f(sv[e] - base);
+            lsum[u] = lsum[u] * corr + (((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7])));
+            mrun[u] = mn;
+            u32x4 pb;
+#pragma unroll
+            for (int w2 = 0; w2 < 4; ++w2) pb[w2] = kv_pack2<KVDT>(pv[2 * w2], pv[2 * w2 + 1]);
+            if (__any(corr != 1.f)) {                        // the running maximum moved in some lane
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                    for (int jj = 0; jj < 4; ++jj) o[u][mb][jj] *= corr;
+            }
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) o[u][mb] = mma_kv<KVDT>(vf[mb], pb, o[u][mb]);
+        }
+    }
+
+    // ---- the two key groups' (max, sum, output) through LDS, then the o product's input
+#pragma unroll
+    for (int u = 0; u < QTW; ++u) {
+        float x0f, x1f;
+        lane_pair_k(lsum[u], 16, x0f, x1f);
+        lsum[u] = x0f + x1f;
+        lane_pair_k(lsum[u], 32, x0f, x1f);
+        lsum[u] = x0f + x1f;
+    }
+    __syncthreads();                                         // no wave reads its step's rows any more
+    f32x4_t* so = (f32x4_t*)&kv[0][0][0][0];                 // [4 QTW tiles][MB][64 lanes]
+    if (kg == 1) {
+#pragma unroll
+        for (int u = 0; u < QTW; ++u) {
+            sml[qw + 4 * u][lane] = float2{mrun[u], lsum[u]};
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) so[((qw + 4 * u) * MB + mb) * 64 + lane] = o[u][mb];
+        }
+    }
+    __syncthreads();
+    if (kg == 1) return;
+#pragma unroll
+    for (int u = 0; u < QTW; ++u) {
+        const int r = r0 + 16 * (qw + 4 * u) + ql;
+        const float2 ml = sml[qw + 4 * u][lane];
+        const float mn = fmaxf(mrun[u], ml.x);               // finite: every query sees its own row
+        const float f0 = __builtin_amdgcn_exp2f(mrun[u] - mn), f1 = __builtin_amdgcn_exp2f(ml.x - mn);
+        const float inv = 1.0f / (lsum[u] * f0 + ml.y * f1);
+        const int m = qtok[u], h = g * gs + r % gs;
+        uint16_t* bp = a.bp + (size_t)(m >> 6) * 64 * a.kp;
+        float* bc = a.bc + (size_t)(m >> 6) * 2 * a.kp;
+#pragma unroll
+        for (int mp = 0; mp < MB / 2; ++mp) {                // 32 dims: one correction
+            float cs = 0.f;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int mb = 2 * mp + q, k = h * D + 16 * mb + 4 * lg;
+                const f32x4_t ob = so[((qw + 4 * u) * MB + mb) * 64 + lane];
+                uint16_t c[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float h16 = f16_to_f32(f32_to_f16((o[u][mb][j] * f0 + ob[j] * f1) * inv));
+                    cs += bp_corr(h16, j);
+                    c[j] = bp_code(h16, j);
+                }
+                if (r < R) __builtin_memcpy(__builtin_assume_aligned(bp + bp_index(m & 63, k), 8), c, 8);
+            }
+            float x0f, x1f;
+            lane_pair_k(cs, 16, x0f, x1f);
+            cs = x0f + x1f;
+            lane_pair_k(cs, 32, x0f, x1f);
+            cs = x0f + x1f;
+            if (r < R && lg == 0) bc[bc_index(m & 63, h * D + 32 * mp)] = cs;
+        }
+    }
+}
+
+hipError_t launch_attention_pf(const PfAttnArgs& a, int head_dim, int n_cus, hipStream_t st) {
+    if (a.n < 1 || a.Hkv < 1 || a.Hq % a.Hkv || a.kp < a.Hq * head_dim || a.kp % 128) return hipErrorInvalidValue;
+    const size_t R = (size_t)a.n * (a.Hq / a.Hkv);
+    // two query tiles per wave (the faster form) where that still gives every CU a workgroup
+    const bool two = (R + 127) / 128 * a.Hkv >= (size_t)n_cus;
+    const dim3 grid((unsigned)((R + (two ? 127 : 63)) / (two ? 128 : 64) * a.Hkv)), block(512);
+    const bool bf = a.kv_dt == DT_BF16;
+#define ATTN_PF(D_)                                                                               \
+    do {                                                                                          \
+        if (bf && two) attn_pf_kernel<D_, DT_BF16, 2><<<grid, block, 0, st>>>(a);                 \
+        else if (bf) attn_pf_kernel<D_, DT_BF16, 1><<<grid, block, 0, st>>>(a);                   \
+        else if (two) attn_pf_kernel<D_, DT_F16, 2><<<grid, block, 0, st>>>(a);                   \
+        else attn_pf_kernel<D_, DT_F16, 1><<<grid, block, 0, st>>>(a);                            \
+    } while (0)
+    if (head_dim == 128) ATTN_PF(128);
+    else if (head_dim == 64) ATTN_PF(64);
+    else return hipErrorInvalidValue;
+#undef ATTN_PF
     return hipGetLastError();
 }
 

@@ -147,9 +147,8 @@ struct Stage {
     int embed_vocab = 0;
     unsigned* embed_err = nullptr;                     // set by a gather that met an id outside the table
     // prefill workspace for pf_rows prompt rows: residual fp32 [rows][H], q|k|v fp32
-    // [rows][NQKV], attention output fp32 [rows][Hq*D], prepared inputs (64-row
-    // blocks; [1]: the down product's)
-    float *pf_x = nullptr, *pf_qkv = nullptr, *pf_attn = nullptr, *pf_bc[2] = {nullptr, nullptr};
+    // [rows][NQKV], prepared inputs (64-row blocks; [1]: the down product's)
+    float *pf_x = nullptr, *pf_qkv = nullptr, *pf_bc[2] = {nullptr, nullptr};
     uint16_t* pf_bp[2] = {nullptr, nullptr};
     float* pf_part = nullptr;                          // sums of the split residual products [splits][rows][H]
     size_t pf_rows = 0;
@@ -186,7 +185,7 @@ struct Stage {
     hipStream_t last_stream = nullptr;
     bool done_used = false;
 
-    std::array<void*, 8> pf_buffers() const { return {pf_x, pf_qkv, pf_attn, pf_bp[0], pf_bp[1], pf_bc[0], pf_bc[1], pf_part}; }
+    std::array<void*, 7> pf_buffers() const { return {pf_x, pf_qkv, pf_bp[0], pf_bp[1], pf_bc[0], pf_bc[1], pf_part}; }
 
     ~Stage() {
         for (hipEvent_t e : prof_ev) (void)hipEventDestroy(e);
@@ -1360,7 +1359,7 @@ int stage_prefill(Stage* st, KVState* kv, int n, const int32_t* positions, const
         HIP_TRY(hipDeviceSynchronize());
         for (void* p : st->pf_buffers())
             if (p) HIP_TRY(hipFree(p));
-        st->pf_x = st->pf_qkv = st->pf_attn = st->pf_bc[0] = st->pf_bc[1] = nullptr;
+        st->pf_x = st->pf_qkv = st->pf_bc[0] = st->pf_bc[1] = nullptr;
         st->pf_bp[0] = st->pf_bp[1] = nullptr;
         st->pf_part = nullptr;
         st->pf_rows = 0;
@@ -1373,7 +1372,6 @@ int stage_prefill(Stage* st, KVState* kv, int n, const int32_t* positions, const
             }
         const size_t kin = (size_t)(std::max(H, Hq * D) + 127) / 128 * 128, kf = (size_t)(F + 127) / 128 * 128;
         if (hipMalloc(&st->pf_x, wrows * H * 4) != hipSuccess || hipMalloc(&st->pf_qkv, wrows * nqkv * 4) != hipSuccess ||
-            hipMalloc(&st->pf_attn, wrows * Hq * D * 4) != hipSuccess ||
             hipMalloc(&st->pf_bp[0], wrows * kin * 2) != hipSuccess || hipMalloc(&st->pf_bp[1], wrows * kf * 2) != hipSuccess ||
             hipMalloc(&st->pf_bc[0], wrows / 64 * 2 * kin * 4) != hipSuccess ||
             hipMalloc(&st->pf_bc[1], wrows / 64 * 2 * kf * 4) != hipSuccess ||
@@ -1384,72 +1382,32 @@ int stage_prefill(Stage* st, KVState* kv, int n, const int32_t* positions, const
         st->pf_rows = wrows;
     }
 
-    // ---------------- one request record per chunk of at most PF_ATT_ROWS rows (the
-    // attention's unit), in one upload: chunk q covers prompt rows [16 q, 16 q + m),
-    // sees the past rows the mask keeps, the earlier chunks' rows and its own rows
-    // causally.  Row numbers (row0, positions, row_item) count from the start of
-    // the chunk's pass.  16-row chunks keep a chunk's query vectors (16 x query
-    // heads per kv head) within one or two tiles per wave, so the attention runs
-    // two workgroups per CU without spilling; the chunks of one context read the
-    // same cache rows, mostly from the caches.
-    constexpr int PF_ATT_ROWS = 16;
-    const int nch = (n + PF_ATT_ROWS - 1) / PF_ATT_ROWS;
-    const int pass_chunks = PF_ROWS / PF_ATT_ROWS;
-    size_t mask_total = 0;
-    for (int q = 0; q < nch; ++q)
-        mask_total += (size_t)P0 + q * PF_ATT_ROWS + std::min(PF_ATT_ROWS, n - q * PF_ATT_ROWS);
-    const size_t off_req = 0;
-    const size_t off_item = align16(off_req + sizeof(ReqDev) * nch);
-    const size_t off_pos = align16(off_item + sizeof(ItemDev) * nch);
-    const size_t off_ritem = align16(off_pos + sizeof(int) * n);
-    const size_t off_mask = align16(off_ritem + sizeof(int) * n);
-    const size_t total = align16(off_mask + mask_total);
+    // ---------------- positions and, if some past row is masked, one bit per cache
+    // row (1: kept; the prompt's own rows are), in one upload
+    bool masked = false;
+    for (int jj = 0; past_mask && jj < P0 && !masked; ++jj) masked = !past_mask[jj];
+    const size_t off_mask = align16(sizeof(int) * n);
+    const size_t n_words = masked ? ((size_t)P0 + n + 31) / 32 : 0;
+    const size_t total = align16(off_mask + 4 * n_words);
     int rc = ensure_meta(st, total);
     if (rc) return rc;
     const int slot_i = st->ring_i;
     st->ring_i = (st->ring_i + 1) % META_RING;
     if (st->meta_ev_used[slot_i]) HIP_TRY(hipEventSynchronize(st->meta_ev[slot_i]));
     uint8_t* hb = st->meta_host[slot_i];
-    const int splits = 2;                              // per (chunk, kv head): the chunks fill the device
-    {
-        size_t moff = 0;
-        for (int q = 0; q < nch; ++q) {
-            const int r0 = q * PF_ATT_ROWS, m = std::min(PF_ATT_ROWS, n - r0);
-            const int qf = q / pass_chunks * pass_chunks;   // first chunk of the pass
-            ReqDev d{};
-            d.P = P0 + r0;
-            d.n = m;
-            d.S = 1;
-            d.row0 = (q - qf) * PF_ATT_ROWS;
-            d.cap = kv->cap;
-            d.mask_off = (int)moff;
-            d.mask_len = P0 + r0 + m;
-            d.rowmask_off = -1;
-            d.item0 = q - qf;
-            d.splits = splits;
-            d.kc = kv->kc;
-            d.vc = kv->vc;
-            d.table = kv->table[kv->cur];
-            ((ReqDev*)(hb + off_req))[q] = d;
-            ((ItemDev*)(hb + off_item))[q] = ItemDev{q - qf, 0, d};
-            for (int i = 0; i < m; ++i) ((int*)(hb + off_ritem))[r0 + i] = q - qf;
-            uint8_t* mk = hb + off_mask + moff;
-            for (int jj = 0; jj < P0; ++jj) mk[jj] = past_mask ? (past_mask[jj] ? 1 : 0) : 1;
-            std::memset(mk + P0, 1, (size_t)r0 + m);
-            moff += (size_t)P0 + r0 + m;
-        }
-        std::memcpy(hb + off_pos, positions, sizeof(int) * n);
+    std::memcpy(hb, positions, sizeof(int) * n);
+    if (masked) {
+        uint32_t* w = (uint32_t*)(hb + off_mask);
+        std::memset(w, 0xFF, 4 * n_words);
+        for (int jj = 0; jj < P0; ++jj)
+            if (!past_mask[jj]) w[jj >> 5] &= ~(1u << (jj & 31));
     }
     uint8_t* db = st->meta_dev;
     HIP_TRY(hipMemcpyAsync(db, hb, total, hipMemcpyHostToDevice, s));
     HIP_TRY(hipEventRecord(st->meta_ev[slot_i], s));
     st->meta_ev_used[slot_i] = true;
-    if ((size_t)PF_ROWS * Hq * splits * (D + 2) > (size_t)MAX_ROWS * Hq * ATTN_MAX_SPLITS * (D + 4))
-        return fail(STAGE_E_UNSUPPORTED, "attention partials of a prefill pass exceed the workspace");
 
-    // ---------------- passes of at most PF_ROWS rows, each through every layer: the
-    // products take all of a pass's rows at once (gemm_pf_kernel), the attention
-    // one 64-row chunk at a time (its keys include the earlier chunks' rows)
+    // ---------------- passes of at most PF_ROWS rows, each through every layer
     const int kin = (std::max(H, Hq * D) + 127) / 128 * 128, kf = (F + 127) / 128 * 128;   // k of the two prepared inputs
     auto pf = [&](const DevMat& mat, int rows, int epi) {
         PfArgs a{};
@@ -1520,50 +1478,33 @@ int stage_prefill(Stage* st, KVState* kv, int n, const int32_t* positions, const
                 HIP_TRY(launch_gemm_pf(a, s));
             }
             HIP_TRY(prof_mark(st, STAGE_KERNEL_QKV, false, s));
-            // the pass's k and v rows into the cache, then the causal attention of all its
-            // 16-row chunks in one launch (each a request whose past includes the
-            // earlier chunks' rows); the output goes to the o product as prepared blocks
+            // the pass's k and v rows into the cache, then its causal attention, whose
+            // output is the o product's input
             HIP_TRY(prof_mark(st, STAGE_KERNEL_ATTN, true, s));
             {
                 const size_t lstride = (size_t)Hkv * kv->cap * D;   // one slot
-                HIP_TRY(launch_kv_rope_append(st->pf_qkv, nqkv, (const int*)(db + off_pos) + p0, st->rope, pr, P0 + p0, Hq, Hkv,
+                HIP_TRY(launch_kv_rope_append(st->pf_qkv, nqkv, (const int*)db + p0, st->rope, pr, P0 + p0, Hq, Hkv,
                                               D, kv->kc + (size_t)l * lstride, kv->vc + (size_t)l * lstride, kv->cap,
                                               first ? kv->table[kv->cur] : nullptr, dt_code(c.kv_dtype), s));
-                const int q0 = p0 / PF_ATT_ROWS, nq = (pr + PF_ATT_ROWS - 1) / PF_ATT_ROWS;
-                AttnArgs a{};
+                PfAttnArgs a{};
                 a.qkv = st->pf_qkv;
                 a.qkv_ld = nqkv;
-                a.out = st->pf_attn;
-                a.out_ld = Hq * D;
-                a.meta.reqs = (const ReqDev*)(db + off_req) + q0;
-                a.meta.items = (const ItemDev*)(db + off_item) + q0;
-                a.meta.positions = (const int*)(db + off_pos) + p0;
-                a.meta.row_item = (const int*)(db + off_ritem) + p0;
-                a.meta.masks = db + off_mask;
-                a.meta.n_items = nq;
-                a.meta.M = pr;
-                a.meta.n_req = nq;
+                a.pos = (const int*)db + p0;
                 a.rope = st->rope;
-                a.layer = l;
+                a.kl = kv->kc + (size_t)l * lstride;
+                a.vl = kv->vc + (size_t)l * lstride;
+                a.cap = kv->cap;
+                a.P = P0 + p0;
+                a.n = pr;
                 a.Hq = Hq;
                 a.Hkv = Hkv;
                 a.kv_dt = dt_code(c.kv_dtype);
+                a.mask = masked ? (const uint32_t*)(db + off_mask) : nullptr;
                 a.qscale = (float)(1.4426950408889634 / std::sqrt((double)D));
-                a.part = st->apart;
-                a.counters = st->acnt;
-                a.nsplit_max = splits;
-                a.vector_path = st->attn_vector;
-                {                                            // the direct-load form: the longest chunk's split fits
-                    const int Lmax = P0 + p0 + pr;
-                    int sl = std::max(ATTN_MIN_SPLIT, (Lmax + splits - 1) / splits);
-                    sl = (sl + KGROUPS - 1) / KGROUPS * KGROUPS;
-                    a.dma = st->attn_dma && sl <= 1024 && lstride * 2 <= 0xFFFFFFF0ull ? 1 : 0;
-                }
-                a.bp_out = st->pf_bp[0];
-                a.bc_out = st->pf_bc[0];
+                a.bp = st->pf_bp[0];
+                a.bc = st->pf_bc[0];
                 a.kp = kin;
-                a.no_append = 1;
-                HIP_TRY(launch_attention(a, D, (Hq / Hkv) * PF_ATT_ROWS, s));
+                HIP_TRY(launch_attention_pf(a, D, st->n_cus, s));
             }
             HIP_TRY(prof_mark(st, STAGE_KERNEL_ATTN, false, s));
             // x = residual + o W_o^T

@@ -2493,13 +2493,16 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
     __shared__ __attribute__((aligned(16))) uint8_t kv[2][2][2][SB];   // [key group][buffer][K, V]
     __shared__ float2 sml[4 * QTW][64];
     static_assert(sizeof(kv) >= (size_t)4 * QTW * MB * 1024, "merge staging");
-    const int g = blockIdx.x % a.Hkv, blk = gridDim.x / a.Hkv - 1 - blockIdx.x / a.Hkv;   // longest first
+    // (divisions and clamps leave uniform values in vector registers: readfirstlane
+    // keeps what the buffer resources are made of scalar)
+    const int g = __builtin_amdgcn_readfirstlane(blockIdx.x % a.Hkv);
+    const int blk = __builtin_amdgcn_readfirstlane((int)(gridDim.x / a.Hkv - 1 - blockIdx.x / a.Hkv));   // longest first
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kg = wave >> 2, qw = wave & 3, tg = tid & 255;
     const int ql = lane & 15, lg = lane >> 4;
     const int Hq = a.Hq, gs = Hq / a.Hkv;
     const int R = a.n * gs, r0 = blk * 64 * QTW;
-    const int kend = a.P + (min(R, r0 + 64 * QTW) - 1) / gs + 1;   // keys the block's last query sees
+    const int kend = __builtin_amdgcn_readfirstlane(a.P + (min(R, r0 + 64 * QTW) - 1) / gs + 1);   // keys the block's last query sees
     const int nsteps = (kend + AK - 1) / AK;
     const uint16_t* kh = a.kl + (size_t)g * a.cap * D;
     const uint16_t* vh = a.vl + (size_t)g * a.cap * D;
@@ -2510,7 +2513,7 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
     u32x4 rk[NL], rv[NL];
     uint32_t word = 0u;                                      // key mask of the step held in rk, rv
     auto ld = [&](int st) {
-        const uint32_t bytes = (uint32_t)max(0, min(AK, kend - AK * st)) * RB;   // later rows read as zeros
+        const uint32_t bytes = __builtin_amdgcn_readfirstlane(max(0, min(AK, kend - AK * st)) * RB);   // later rows read as zeros
         const size_t base = (size_t)min(st, nsteps - 1) * AK * D;
         const __amdgpu_buffer_rsrc_t bk = attn_rsrc(kh + base, bytes), bv = attn_rsrc(vh + base, bytes);
 #pragma unroll
@@ -2543,7 +2546,12 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
     // ---- this wave's query tiles: rotated, scaled, split into rounded part and residual
     u32x4 qh[QTW][DB], qr[QTW][DB];
     int qtok[QTW];
-    float mrun[QTW], lsum[QTW];
+    float base[QTW];                                         // what is subtracted from the scores (-inf: no key seen yet)
+    f32x4_t lacc[QTW];                                       // sums of the rounded probabilities, the same in every row
+    u32x4 ones;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ones[e] = KVDT == DT_BF16 ? 0x3F803F80u : 0x3C003C00u;
+    f32x4_t nb[QTW];                                         // -base (0 before the first key), the score products' start
     f32x4_t o[QTW][MB];
 #pragma unroll
     for (int u = 0; u < QTW; ++u) {
@@ -2551,8 +2559,8 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
         const bool ok = r < R;
         const int i = ok ? r / gs : a.n - 1, h = g * gs + (ok ? r % gs : 0);   // the last row stands in past the end
         qtok[u] = i;
-        mrun[u] = -INFINITY;
-        lsum[u] = 0.f;
+        base[u] = -INFINITY;
+        nb[u] = lacc[u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
         const float* qrow = a.qkv + (size_t)i * a.qkv_ld + (size_t)h * D;
         const float2* rp = a.rope + (size_t)a.pos[i] * HALF;
 #pragma unroll
@@ -2580,7 +2588,7 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) o[u][mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
-    const int tok0 = min(R - 1, r0 + 16 * qw) / gs;          // the wave's first token: steps up to it are causal for all
+    const int tok0 = __builtin_amdgcn_readfirstlane(min(R - 1, r0 + 16 * qw) / gs);          // the wave's first token: steps up to it are causal for all
 
     uint32_t cword = word;
     put(0);
@@ -2596,12 +2604,25 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
         const uint8_t* kb = kv[kg][buf][0];
         const uint8_t* vb = kv[kg][buf][1];
         u32x4 kf0[DB], kf1[DB], vf[MB];
+        f32x4_t s0[QTW], s1[QTW];
 #pragma unroll
         for (int ib = 0; ib < DB; ++ib) {
             const int c = 4 * ib + lg;
             kf0[ib] = *(const u32x4*)&kb[ql * RB + 16 * (c ^ (ql % NCH))];
             kf1[ib] = *(const u32x4*)&kb[(16 + ql) * RB + 16 * (c ^ ((16 + ql) % NCH))];
         }
+#pragma unroll
+        for (int u = 0; u < QTW; ++u) {
+            s0[u] = s1[u] = nb[u];
+#pragma unroll
+            for (int ib = 0; ib < DB; ++ib) {
+                s0[u] = mma_kv<KVDT>(kf0[ib], qh[u][ib], s0[u]);
+                s1[u] = mma_kv<KVDT>(kf1[ib], qh[u][ib], s1[u]);
+                s0[u] = mma_kv<KVDT>(kf0[ib], qr[u][ib], s0[u]);
+                s1[u] = mma_kv<KVDT>(kf1[ib], qr[u][ib], s1[u]);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);                   // the value reads take the key fragments' registers
         // value fragments: read h gives keys 16 h + 4 lg + e; this lane supplies
         // key 16 h + 4 lg + ql / 4, dims 16 mb + 4 (ql mod 4) .. + 3
 #pragma unroll
@@ -2622,20 +2643,13 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
         const int kbase = AK * st + 4 * lg;
 #pragma unroll
         for (int u = 0; u < QTW; ++u) {
-            f32x4_t s0 = f32x4_t{0.f, 0.f, 0.f, 0.f}, s1 = s0;
-#pragma unroll
-            for (int ib = 0; ib < DB; ++ib) {
-                s0 = mma_kv<KVDT>(kf0[ib], qh[u][ib], s0);
-                s1 = mma_kv<KVDT>(kf1[ib], qh[u][ib], s1);
-                s0 = mma_kv<KVDT>(kf0[ib], qr[u][ib], s0);
-                s1 = mma_kv<KVDT>(kf1[ib], qr[u][ib], s1);
-            }
             float sv[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) sv[e] = e < 4 ? s0[e] : s1[e - 4];
+            for (int e = 0; e < 8; ++e) sv[e] = e < 4 ? s0[u][e] : s1[u][e - 4];
             if (!all) {
                 const int last = a.P + qtok[u] - kbase;      // keys up to kbase + last are causal
-                const uint32_t vbits = w0 >> (4 * lg);
+                uint32_t vbits = w0 >> (4 * lg);
+                asm volatile("" : "+v"(vbits));              // the bit tests stay inside the branch
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const int ko = (e < 4) ? e : 12 + e;
@@ -2645,49 +2659,52 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
             float mx = sv[0];
 #pragma unroll
             for (int e = 1; e < 8; ++e) mx = fmaxf(mx, sv[e]);
-            float x0f, x1f;
-            lane_pair_k(mx, 16, x0f, x1f);
-            mx = fmaxf(x0f, x1f);
-            lane_pair_k(mx, 32, x0f, x1f);
-            mx = fmaxf(x0f, x1f);
-            const float mn = fmaxf(mrun[u], mx);
-            // no key seen yet (mn = -inf): base 0 makes every term and the correction 0
-            const float base = mn == -INFINITY ? 0.f : mn;
-            const float corr = __builtin_amdgcn_exp2f(mrun[u] - base);
-            float pv[8];
+            // A step in which no query's largest score rises has no exchange between
+            // lanes and no correction.  (Letting the base lag by up to 8 saved more,
+            // but the largest key's probability was then rounded too: the error
+            // against 64 bits grew by 3%.)  The sum is taken of the rounded
+            // probabilities, one product with ones.
+            if (__any(mx > (base[u] == -INFINITY ? -INFINITY : 0.f))) {
+                float x0f, x1f;
+                lane_pair_k(mx, 16, x0f, x1f);
+                mx = fmaxf(x0f, x1f);
+                lane_pair_k(mx, 32, x0f, x1f);
+                mx = fmaxf(x0f, x1f);                        // the query's largest score of the step, less the old base
+                // a first key sets the base; no key yet leaves it; else it only rises
+                const bool first = base[u] == -INFINITY;
+                const float up = first ? (mx == -INFINITY ? 0.f : mx) : fmaxf(mx, 0.f);
+                const float corr = first ? 0.f : __builtin_amdgcn_exp2f(-up);
+                base[u] = first ? mx : base[u] + up;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) pv[e] = __builtin_amdgcn_exp2f(sv[e] - base);
-            lsum[u] = lsum[u] * corr + (((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7])));
-            mrun[u] = mn;
-            u32x4 pb;
+                for (int j = 0; j < 4; ++j) nb[u][j] -= up;
 #pragma unroll
-            for (int w2 = 0; w2 < 4; ++w2) pb[w2] = kv_pack2<KVDT>(pv[2 * w2], pv[2 * w2 + 1]);
-            if (__any(corr != 1.f)) {                        // the running maximum moved in some lane
+                for (int j = 0; j < 4; ++j) lacc[u][j] *= corr;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) sv[e] -= up;
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
                     for (int jj = 0; jj < 4; ++jj) o[u][mb][jj] *= corr;
             }
+            float pv[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) pv[e] = __builtin_amdgcn_exp2f(sv[e]);
+            u32x4 pb;
+#pragma unroll
+            for (int w2 = 0; w2 < 4; ++w2) pb[w2] = kv_pack2<KVDT>(pv[2 * w2], pv[2 * w2 + 1]);
+            lacc[u] = mma_kv<KVDT>(ones, pb, lacc[u]);
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) o[u][mb] = mma_kv<KVDT>(vf[mb], pb, o[u][mb]);
         }
     }
 
-    // ---- the two key groups' (max, sum, output) through LDS, then the o product's input
-#pragma unroll
-    for (int u = 0; u < QTW; ++u) {
-        float x0f, x1f;
-        lane_pair_k(lsum[u], 16, x0f, x1f);
-        lsum[u] = x0f + x1f;
-        lane_pair_k(lsum[u], 32, x0f, x1f);
-        lsum[u] = x0f + x1f;
-    }
+    // ---- the two key groups' (base, sum, output) through LDS, then the o product's input
     __syncthreads();                                         // no wave reads its step's rows any more
     f32x4_t* so = (f32x4_t*)&kv[0][0][0][0];                 // [4 QTW tiles][MB][64 lanes]
     if (kg == 1) {
 #pragma unroll
         for (int u = 0; u < QTW; ++u) {
-            sml[qw + 4 * u][lane] = float2{mrun[u], lsum[u]};
+            sml[qw + 4 * u][lane] = float2{base[u], lacc[u][0]};
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) so[((qw + 4 * u) * MB + mb) * 64 + lane] = o[u][mb];
         }
@@ -2698,9 +2715,9 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
     for (int u = 0; u < QTW; ++u) {
         const int r = r0 + 16 * (qw + 4 * u) + ql;
         const float2 ml = sml[qw + 4 * u][lane];
-        const float mn = fmaxf(mrun[u], ml.x);               // finite: every query sees its own row
-        const float f0 = __builtin_amdgcn_exp2f(mrun[u] - mn), f1 = __builtin_amdgcn_exp2f(ml.x - mn);
-        const float inv = 1.0f / (lsum[u] * f0 + ml.y * f1);
+        const float mn = fmaxf(base[u], ml.x);               // finite: every query sees its own row
+        const float f0 = __builtin_amdgcn_exp2f(base[u] - mn), f1 = __builtin_amdgcn_exp2f(ml.x - mn);
+        const float inv = 1.0f / (lacc[u][0] * f0 + ml.y * f1);
         const int m = qtok[u], h = g * gs + r % gs;
         uint16_t* bp = a.bp + (size_t)(m >> 6) * 64 * a.kp;
         float* bc = a.bc + (size_t)(m >> 6) * 2 * a.kp;
@@ -2733,8 +2750,10 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
 hipError_t launch_attention_pf(const PfAttnArgs& a, int head_dim, int n_cus, hipStream_t st) {
     if (a.n < 1 || a.Hkv < 1 || a.Hq % a.Hkv || a.kp < a.Hq * head_dim || a.kp % 128) return hipErrorInvalidValue;
     const size_t R = (size_t)a.n * (a.Hq / a.Hkv);
-    // two query tiles per wave (the faster form) where that still gives every CU a workgroup
-    const bool two = (R + 127) / 128 * a.Hkv >= (size_t)n_cus;
+    // one workgroup runs per CU; two query tiles per wave take about 5/3 of one
+    // tile's time a step, so they pay where they save a round of workgroups
+    const size_t w1 = (R + 63) / 64 * a.Hkv, w2 = (R + 127) / 128 * a.Hkv;
+    const bool two = 5 * ((w2 + n_cus - 1) / n_cus) <= 3 * ((w1 + n_cus - 1) / n_cus);
     const dim3 grid((unsigned)((R + (two ? 127 : 63)) / (two ? 128 : 64) * a.Hkv)), block(512);
     const bool bf = a.kv_dt == DT_BF16;
 #define ATTN_PF(D_)                                                                               \

@@ -577,15 +577,30 @@ __device__ __forceinline__ void row_factors_finish(const GemvArgs& a, int K, boo
     }
 }
 
+// A bounds-checked buffer over `bytes` at p (loads past the end return zero).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
+}
+template <int AUX = 0>                                        // 2: non-temporal
+__device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t soff) {
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, AUX));
+}
+
 // Product of the prepared input with one matrix: a workgroup's 4 waves take
 // one 64-row tile and 4 consecutive ranges of a.kg groups of 128 k; blockIdx.y
 // is the split of K (fixed per matrix, so results do not depend on M).  A lane
 // loads 16 bytes of codes per row block and group (chunk 4 gi + lane / 16 of row
-// 16 rt + lane mod 16): dword i of it is the A operand of the group's i-th
-// product, whose k are 32 (4 gi + lane / 16) + 8 i + e; the B operand of that
-// product is read from the prepared row at the same k.
-template <int NCB>
-__global__ __launch_bounds__(256, NCB <= 2 ? 2 : 1) void gemm_bp_kernel(GemvArgs a) {
+// 16 rt + lane mod 16): dword i of it, decoded, is an operand of the group's
+// i-th product, whose k are 32 (4 gi + lane / 16) + 8 i + e; the other operand
+// is read from the prepared rows at the same k.  The prepared rows are the
+// products' rows and the weight rows their columns, so a lane's results belong
+// to one weight row (one scale) and four input rows, whose corrections are the
+// products' starting value: one fp32 product of the 16 rows' four corrections
+// with -1.  That leaves one multiply-add per result and group.
+// Z = 2: 33..64 rows, as two workgroups of 32 rows per tile that run one after
+// the other on one XCD (the second finds the codes in its L2).
+template <int NCB, int Z>
+__global__ __launch_bounds__(256, 2) void gemm_bp_kernel(GemvArgs a) {
     constexpr int MP = 16 * NCB;
     constexpr int NV = MP * 64 / 256;
     __shared__ float red[4][MP][65];
@@ -594,33 +609,36 @@ __global__ __launch_bounds__(256, NCB <= 2 ? 2 : 1) void gemm_bp_kernel(GemvArgs
     __shared__ int last_s;
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: scalar loop control
     const int l16 = lane & 15, lg = lane >> 4;
-    const int t = blockIdx.x, s = blockIdx.y;
+    const int t = Z == 1 ? (int)blockIdx.x : (int)((blockIdx.x >> 4) * 8 + (blockIdx.x & 7)), s = blockIdx.y;
+    const int m0 = Z == 1 ? 0 : 32 * ((blockIdx.x >> 3) & 1);   // first row
     const PackedMat W = a.W;
+    if (Z > 1 && t >= W.ntiles) return;                         // whole workgroup
     const int M = a.M, K = W.k;
     const int g0 = (4 * s + w) * a.kg, g1 = min(W.ngroups, g0 + a.kg);
-    const int kc = a.kp / 32;
     uint32_t magic = 0x64006400u;
     asm volatile("" : "+v"(magic));
+    const __amdgpu_buffer_rsrc_t rw = buf_rsrc(W.w + (size_t)t * W.nchunk * 1024, (uint32_t)W.nchunk * 1024);
+    const __amdgpu_buffer_rsrc_t rsc = buf_rsrc(W.s + (size_t)t * W.ngroups * 64, (uint32_t)W.ngroups * 128);
+    const __amdgpu_buffer_rsrc_t rb = buf_rsrc(a.bp_in, (uint32_t)a.kp * 128);
+    const __amdgpu_buffer_rsrc_t rc = buf_rsrc(a.bc_in, (uint32_t)a.kp * 8);
+    const uint32_t wo = 16u * (64 * lg + l16), so = 2u * l16, bo = 16u * lane + 256u * m0, co = 16u * (m0 + l16) + 4u * lg;
 
-    auto ldw = [&](int gi, u32x4 (&wv)[4], u32x2 (&sv)[4]) {
+    auto ldw = [&](int gi, u32x4 (&wv)[4], uint16_t (&sv)[4]) {
 #pragma unroll
         for (int rt = 0; rt < 4; ++rt) {
-            wv[rt] = __builtin_nontemporal_load(
-                (const u32x4*)(W.w + (((size_t)t * W.nchunk + 4 * gi + lg) * 64 + 16 * rt + l16) * 16));
-            sv[rt] = *(const u32x2*)(W.s + ((size_t)t * W.ngroups + gi) * 64 + 16 * rt + 4 * lg);
+            wv[rt] = buf_load16<Z == 1 ? 2 /* nt */ : 0>(rw, wo, 4096 * gi + 256 * rt);
+            sv[rt] = __builtin_amdgcn_raw_buffer_load_b16(rsc, so, 128 * gi + 32 * rt, 0);
         }
     };
-    // prepared operand and corrections of one group as stored; entries at k >= K
-    // (past the end of a ragged last group) are dropped when the group computes,
-    // so nothing waits for these loads before then
-    auto ldb = [&](int gi, u32x4 (&bv)[NCB][4], float4 (&cv)[NCB]) {
+    // prepared operand and corrections (row l16, chunk lg) of one group as stored;
+    // entries at k >= K (past the end of a ragged last group) are dropped when the
+    // group computes, so nothing waits for these loads before then
+    auto ldb = [&](int gi, u32x4 (&bv)[NCB][4], float (&cv)[NCB]) {
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) {
-            const int m = 16 * cb + l16;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                bv[cb][i] = *(const u32x4*)(a.bp_in + ((((size_t)gi * 16 + cb * 4 + i) * 64 + lane) << 3));
-            cv[cb] = *(const float4*)(a.bc_in + ((size_t)gi * 64 + m) * 4);
+            for (int i = 0; i < 4; ++i) bv[cb][i] = buf_load16<0>(rb, bo, 16384 * gi + 4096 * cb + 1024 * i);
+            cv[cb] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rc, co, 1024 * gi + 256 * cb, 0));
         }
     };
 
@@ -637,21 +655,11 @@ __global__ __launch_bounds__(256, NCB <= 2 ? 2 : 1) void gemm_bp_kernel(GemvArgs
     // before the group computes, so no branch or select sits between a load and
     // its use and the compiler waits for exactly the loads each product needs.
     u32x4 wr[2][4], br[2][NCB][4];
-    u32x2 sr[2][4];
-    float4 cr[2][NCB];
-    // The products of a group are issued k-slice by k-slice (i outer): the 4 NCB
-    // accumulators of the tile are independent, so no product waits for the one
-    // before it; each accumulator still adds its four slices in order.
-    auto compute = [&](int gi, const u32x4 (&wv)[4], const u32x2 (&sv)[4], u32x4 (&bv)[NCB][4], const float4 (&cq)[NCB]) {
+    uint16_t sr[2][4];
+    float cr[2][NCB];
+    auto compute = [&](int gi, const u32x4 (&wv)[4], const uint16_t (&sv)[4], u32x4 (&bv)[NCB][4], float (&cv)[NCB]) {
         const int kb = 128 * gi;
-        float cv[NCB];
-        if (kb + 128 <= K) {                             // a whole group (uniform)
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) {
-                const float4 c4 = cq[cb];
-                cv[cb] = (c4.x + c4.y) + (c4.z + c4.w);
-            }
-        } else {
+        if (kb + 128 > K) {                              // a ragged last group (uniform)
 #pragma unroll
             for (int cb = 0; cb < NCB; ++cb) {
 #pragma unroll
@@ -660,51 +668,42 @@ __global__ __launch_bounds__(256, NCB <= 2 ? 2 : 1) void gemm_bp_kernel(GemvArgs
 #pragma unroll
                     for (int e = 0; e < 4; ++e) bv[cb][i][e] = in ? bv[cb][i][e] : 0u;
                 }
-                const float4 c4 = cq[cb];
-                cv[cb] = ((kb < K ? c4.x : 0.f) + (kb + 32 < K ? c4.y : 0.f)) + ((kb + 64 < K ? c4.z : 0.f) + (kb + 96 < K ? c4.w : 0.f));
+                cv[cb] = kb + 32 * lg < K ? cv[cb] : 0.f;
             }
         }
-        f32x4_t c[4][NCB];
+        f32x4_t c0[NCB];
 #pragma unroll
-        for (int rt = 0; rt < 4; ++rt)
+        for (int cb = 0; cb < NCB; ++cb)
+            c0[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(cv[cb], -1.0f, f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
 #pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) c[rt][cb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int rt = 0; rt < 4; ++rt) {
+            half8_t B[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            half8_t A[4];
-#pragma unroll
-            for (int rt = 0; rt < 4; ++rt) {
+            for (int i = 0; i < 4; ++i) {
                 const uint32_t x = wv[rt][i], y = x >> 8;
                 u32x4 av;
                 av[0] = and_or_u32(0x000F000Fu, x, magic);
                 av[1] = and_or_u32(0x00F000F0u, x, magic);
                 av[2] = and_or_u32(0x000F000Fu, y, magic);
                 av[3] = and_or_u32(0x00F000F0u, y, magic);
-                A[rt] = __builtin_bit_cast(half8_t, av);
+                B[i] = __builtin_bit_cast(half8_t, av);
             }
+            const float scl = f16_to_f32(sv[rt]);
+            f32x4_t c[NCB];
 #pragma unroll
-            for (int rt = 0; rt < 4; ++rt)
+            for (int i = 0; i < 4; ++i)
 #pragma unroll
                 for (int cb = 0; cb < NCB; ++cb)
-                    c[rt][cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[rt], __builtin_bit_cast(half8_t, bv[cb][i]), c[rt][cb], 0, 0, 0);
-        }
-#pragma unroll
-        for (int rt = 0; rt < 4; ++rt) {
-            float scl[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t h = sv[rt][j >> 1];
-                scl[j] = f16_to_f32((uint16_t)((j & 1) ? (h >> 16) : (h & 0xFFFFu)));
-            }
+                    c[cb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, bv[cb][i]), B[i], i == 0 ? c0[cb] : c[cb], 0, 0, 0);
 #pragma unroll
             for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[rt][cb][j] = __builtin_fmaf(scl[j], c[rt][cb][j] - cv[cb], acc[rt][cb][j]);
+                for (int j = 0; j < 4; ++j) acc[rt][cb][j] = __builtin_fmaf(scl, c[cb][j], acc[rt][cb][j]);
         }
     };
     // each tile starts its range at its own group (rotation by the tile index): at
     // any moment the workgroups read different parts of the prepared operand
-    const int n = g1 - g0, rot = n > 0 ? t % n : 0;
+    const int n = g1 - g0, rot = __builtin_amdgcn_readfirstlane(n > 0 ? t % n : 0);
     auto G = [&](int q) {
         q = min(q, n - 1) + rot;
         return g0 + (q >= n ? q - n : q);
@@ -722,13 +721,13 @@ __global__ __launch_bounds__(256, NCB <= 2 ? 2 : 1) void gemm_bp_kernel(GemvArgs
         size_t off[NV];                                  // clamped to a valid element; outside rows are never used
 #pragma unroll
         for (int q = 0; q < NV; ++q) {
-            const int idx = tid + 256 * q, m = min(idx >> 6, M - 1), n = min(t * 64 + (idx & 63), W.n - 1);
+            const int idx = tid + 256 * q, m = min(m0 + (idx >> 6), M - 1), n = min(t * 64 + (idx & 63), W.n - 1);
             off[q] = (size_t)m * a.resid_ld + n;
         }
         load_vals(a.resid, a.resid_dt, off, pres);
         if (a.bp_out) {                                  // raw now, converted once every load is out
             pgam_bits = a.gamma_next[min(t * 64 + (tid & 63), W.n - 1)];
-            prs = a.rs_in[min(tid, M - 1)];
+            prs = a.rs_in[min(m0 + tid, M - 1)];
         }
     }
     // factor of each row (rs / c for a deferred RMSNorm input, else 1): its
@@ -775,13 +774,13 @@ __global__ __launch_bounds__(256, NCB <= 2 ? 2 : 1) void gemm_bp_kernel(GemvArgs
             compute(G(q), wr[0], sr[0], br[0], cr[0]);
         }
     }
-    // ---- the 4 waves' sums of each output (lane: rows 16 rt + 4 lg + j of column 16 cb + l16), in wave order
+    // ---- the 4 waves' sums of each output (lane: weight row 16 rt + l16 of input rows 16 cb + 4 lg + j), in wave order
 #pragma unroll
     for (int rt = 0; rt < 4; ++rt)
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) red[w][16 * cb + l16][16 * rt + 4 * lg + j] = acc[rt][cb][j];
+            for (int j = 0; j < 4; ++j) red[w][16 * cb + 4 * lg + j][16 * rt + l16] = acc[rt][cb][j];
     __syncthreads();
     float vals[NV];
 #pragma unroll
@@ -796,10 +795,10 @@ __global__ __launch_bounds__(256, NCB <= 2 ? 2 : 1) void gemm_bp_kernel(GemvArgs
 #pragma unroll
         for (int q = 0; q < NV; ++q) {
             const int idx = tid + 256 * q;
-            if (idx < M * 64)
-                store_coherent(&a.partial[((size_t)s * M + (idx >> 6)) * ldp + t * 64 + (idx & 63)], vals[q]);
+            if (m0 + (idx >> 6) < M)
+                store_coherent(&a.partial[((size_t)s * M + m0 + (idx >> 6)) * ldp + t * 64 + (idx & 63)], vals[q]);
         }
-        if (!last_arrival(&a.counters[t], (unsigned)a.ksplit, &last_s)) return;
+        if (!last_arrival(&a.counters[Z == 1 ? t : 2 * t + (m0 >> 5)], (unsigned)a.ksplit, &last_s)) return;
         const size_t stride = (size_t)M * ldp;
 #pragma unroll
         for (int q = 0; q < NV; ++q) vals[q] = 0.f;
@@ -808,10 +807,10 @@ __global__ __launch_bounds__(256, NCB <= 2 ? 2 : 1) void gemm_bp_kernel(GemvArgs
 #pragma unroll
             for (int q = 0; q < NV; ++q) {
                 const int idx = tid + 256 * q;
-                const float* pp = &a.partial[(size_t)(idx >> 6) * ldp + t * 64 + (idx & 63)];
+                const float* pp = &a.partial[(size_t)(m0 + (idx >> 6)) * ldp + t * 64 + (idx & 63)];
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    b4[q][e] = (idx < M * 64 && s0 + e < a.ksplit) ? load_coherent(pp + (s0 + e) * stride) : 0.f;
+                    b4[q][e] = (m0 + (idx >> 6) < M && s0 + e < a.ksplit) ? load_coherent(pp + (s0 + e) * stride) : 0.f;
             }
 #pragma unroll
             for (int q = 0; q < NV; ++q)
@@ -825,8 +824,8 @@ __global__ __launch_bounds__(256, NCB <= 2 ? 2 : 1) void gemm_bp_kernel(GemvArgs
 #pragma unroll
         for (int q = 0; q < NV; ++q) {
             const int idx = tid + 256 * q;
-            if (idx < M * 64) {
-                const int m = idx >> 6, n = t * 64 + (idx & 63);
+            if (m0 + (idx >> 6) < M) {
+                const int m = m0 + (idx >> 6), n = t * 64 + (idx & 63);
                 if (n < W.n) a.out[(size_t)m * a.out_ld + n] = vals[q] * fs[m];
             }
         }
@@ -839,7 +838,7 @@ __global__ __launch_bounds__(256, NCB <= 2 ? 2 : 1) void gemm_bp_kernel(GemvArgs
             uint16_t gbits[NV];
 #pragma unroll
             for (int q = 0; q < NV; ++q) {
-                const int idx = tid + 256 * q, m = min(idx >> 6, M - 1), n = min(t * 64 + (idx & 63), W.n - 1);
+                const int idx = tid + 256 * q, m = min(m0 + (idx >> 6), M - 1), n = min(t * 64 + (idx & 63), W.n - 1);
                 off[q] = (size_t)m * a.resid_ld + n;
                 gbits[q] = a.bp_out ? a.gamma_next[n] : (uint16_t)0;
                 ers[q] = a.bp_out ? a.rs_in[m] : 0.f;
@@ -851,13 +850,13 @@ __global__ __launch_bounds__(256, NCB <= 2 ? 2 : 1) void gemm_bp_kernel(GemvArgs
 #pragma unroll
         for (int q = 0; q < NV; ++q) {
             const int idx = tid + 256 * q;
-            const int m = idx >> 6, r = idx & 63;                     // one row per wave: whole waves take part
+            const int m = m0 + (idx >> 6), r = idx & 63;              // one row per wave: whole waves take part
             const int n = t * 64 + r;
             const bool ok = m < M && n < W.n;
             float xn = 0.f;
             if (ok) {
                 float xr;
-                if constexpr (PRE) xr = sres[m][r];
+                if constexpr (PRE) xr = sres[m - m0][r];
                 else xr = xres[q];
                 xn = xr + vals[q] * fs[m];
                 a.out[(size_t)m * a.out_ld + n] = xn;
@@ -869,7 +868,7 @@ __global__ __launch_bounds__(256, NCB <= 2 ? 2 : 1) void gemm_bp_kernel(GemvArgs
             if (a.bp_out && m < M) {                                    // the next product's input
                 float c, gm;
                 if constexpr (PRE) {
-                    c = srs[m];
+                    c = srs[m - m0];
                     gm = sgam[r];
                 } else {
                     c = ers[q];
@@ -886,7 +885,7 @@ __global__ __launch_bounds__(256, NCB <= 2 ? 2 : 1) void gemm_bp_kernel(GemvArgs
 #pragma unroll
         for (int q = 0; q < NV; ++q) {
             const int idx = tid + 256 * q;
-            const int m = idx >> 6, r = idx & 63;
+            const int m = m0 + (idx >> 6), r = idx & 63;
             const int n = t * 64 + r;
             const bool ok = m < M && n < W.n;
             const float v = ok ? vals[q] * fs[m] : -INFINITY;
@@ -900,17 +899,17 @@ __global__ __launch_bounds__(256, NCB <= 2 ? 2 : 1) void gemm_bp_kernel(GemvArgs
 #pragma unroll
         for (int q = 0; q < NV; ++q) {
             const int idx = tid + 256 * q;
-            if (idx < M * 64) red[0][idx >> 6][idx & 63] = vals[q] * fs[idx >> 6];
+            if (m0 + (idx >> 6) < M) red[0][idx >> 6][idx & 63] = vals[q] * fs[m0 + (idx >> 6)];
         }
         __syncthreads();
         for (int i0 = 0; i0 < MP * 32; i0 += 256) {                    // whole waves: two rows each
             const int idx = i0 + tid;
-            const int m = idx >> 5, r = idx & 31;
+            const int ml = idx >> 5, m = m0 + ml, r = idx & 31;
             const int f = t * 32 + r;
             const bool ok = m < M && f < a.n_valid;
             float y = 0.f;
             if (ok) {
-                const float gt = red[0][m][r], up = red[0][m][r + 32];
+                const float gt = red[0][ml][r], up = red[0][ml][r + 32];
                 y = (gt / (1.0f + expf(-gt))) * up;
                 a.out[(size_t)m * a.out_ld + f] = y;
             }
@@ -922,24 +921,13 @@ __global__ __launch_bounds__(256, NCB <= 2 ? 2 : 1) void gemm_bp_kernel(GemvArgs
 hipError_t launch_gemm_bp(const GemvArgs& a, hipStream_t st) {
     if (a.M < 1 || a.M > 64 || a.W.gchunks != 4 || a.kg < 1 || a.kp % 128) return hipErrorInvalidValue;
     const dim3 grid(a.W.ntiles, a.ksplit), block(256);
-    switch ((a.M + 15) / 16) {
-        case 1: gemm_bp_kernel<1><<<grid, block, 0, st>>>(a); break;
-        case 2: gemm_bp_kernel<2><<<grid, block, 0, st>>>(a); break;
-        case 3: gemm_bp_kernel<3><<<grid, block, 0, st>>>(a); break;
-        default: gemm_bp_kernel<4><<<grid, block, 0, st>>>(a); break;
-    }
+    if (a.M <= 16) gemm_bp_kernel<1, 1><<<grid, block, 0, st>>>(a);
+    else if (a.M <= 32) gemm_bp_kernel<2, 1><<<grid, block, 0, st>>>(a);
+    else gemm_bp_kernel<2, 2><<<dim3((a.W.ntiles + 7) / 8 * 16, a.ksplit), block, 0, st>>>(a);
     return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ prefill product
-
-// A bounds-checked buffer over `bytes` at p (loads past the end return zero).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t attn_rsrc(const void* p, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
-}
-__device__ __forceinline__ u32x4 pf_load16(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t soff) {
-    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0));
-}
 
 // Eight consecutive values at element offset i of p (fp32 at 16-byte aligned
 // offsets; 16-bit values at any 2-byte aligned address).
@@ -1111,10 +1099,10 @@ __global__ __launch_bounds__(256, 2) void gemm_pf_kernel(PfArgs a) {
     const int K = W.k;
     const int g0 = s * a.kg, ng = min((K + 127) / 128, g0 + a.kg);   // this split's groups: g0 .. ng - 1
     // buffer resources: uniform group offsets, one 32-bit offset per lane
-    const __amdgpu_buffer_rsrc_t rbp = attn_rsrc(a.bp + (size_t)tb * a.bp_blk, (uint32_t)a.bp_blk * 2);
-    const __amdgpu_buffer_rsrc_t rbc = attn_rsrc(a.bc + (size_t)tb * a.bc_blk, (uint32_t)a.bc_blk * 4);
-    const __amdgpu_buffer_rsrc_t rw = attn_rsrc(W.w + (size_t)tt * W.nchunk * 1024, (uint32_t)W.nchunk * 1024);
-    const __amdgpu_buffer_rsrc_t rs = attn_rsrc(W.s + (size_t)tt * W.ngroups * 64, (uint32_t)W.ngroups * 128);
+    const __amdgpu_buffer_rsrc_t rbp = buf_rsrc(a.bp + (size_t)tb * a.bp_blk, (uint32_t)a.bp_blk * 2);
+    const __amdgpu_buffer_rsrc_t rbc = buf_rsrc(a.bc + (size_t)tb * a.bc_blk, (uint32_t)a.bc_blk * 4);
+    const __amdgpu_buffer_rsrc_t rw = buf_rsrc(W.w + (size_t)tt * W.nchunk * 1024, (uint32_t)W.nchunk * 1024);
+    const __amdgpu_buffer_rsrc_t rs = buf_rsrc(W.s + (size_t)tt * W.ngroups * 64, (uint32_t)W.ngroups * 128);
     const uint32_t bo = 16u * tid, co = 4u * tid, wo = 16u * (64 * lg + l16), so = 2u * l16;
     uint32_t magic = 0x64006400u;
     asm volatile("" : "+v"(magic));
@@ -1125,7 +1113,7 @@ __global__ __launch_bounds__(256, 2) void gemm_pf_kernel(PfArgs a) {
     // (thread 4 r + c: chunk c of token r)
     auto ld_b = [&](int g) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) rb[u] = pf_load16(rbp, bo, 16384 * g + 4096 * u);
+        for (int u = 0; u < 4; ++u) rb[u] = buf_load16(rbp, bo, 16384 * g + 4096 * u);
         rc = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rbc, co, 1024 * g, 0));
     };
     auto st_b = [&](int g) {
@@ -1149,7 +1137,7 @@ __global__ __launch_bounds__(256, 2) void gemm_pf_kernel(PfArgs a) {
     u32x4 cw[4];
     uint16_t cs[4];
     auto ld_w = [&](int g, int rt) {
-        cw[rt] = pf_load16(rw, wo, 4096 * g + 256 * rt);
+        cw[rt] = buf_load16(rw, wo, 4096 * g + 256 * rt);
         cs[rt] = __builtin_amdgcn_raw_buffer_load_b16(rs, so, 128 * g + 32 * rt, 0);
     };
     auto decode = [&](const u32x4& v, half8_t (&B)[4]) {
@@ -2122,7 +2110,7 @@ __global__ __launch_bounds__(256, QTW == 1 ? 2 : 1) void attn_dma_kernel(AttnArg
     // this wave carries chunk position l mod NCH of key (NI wave + h) KPI + l / NCH
     const int nsteps = (j1 - j0 + AK - 1) / AK;
     const uint32_t lbytes = (uint32_t)(lstride * 2);
-    const __amdgpu_buffer_rsrc_t rk = attn_rsrc(kl, lbytes), rv = attn_rsrc(vl, lbytes);
+    const __amdgpu_buffer_rsrc_t rk = buf_rsrc(kl, lbytes), rv = buf_rsrc(vl, lbytes);
     const uint32_t smk_a = (uint32_t)(uintptr_t)smk, stab_a = (uint32_t)(uintptr_t)stab;
     const uint32_t kvs_a = (uint32_t)(uintptr_t)&kvs[0][0][0];
     const int cstop = min(j1, P);                            // keys below this come from the cache
@@ -2515,11 +2503,11 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
     auto ld = [&](int st) {
         const uint32_t bytes = __builtin_amdgcn_readfirstlane(max(0, min(AK, kend - AK * st)) * RB);   // later rows read as zeros
         const size_t base = (size_t)min(st, nsteps - 1) * AK * D;
-        const __amdgpu_buffer_rsrc_t bk = attn_rsrc(kh + base, bytes), bv = attn_rsrc(vh + base, bytes);
+        const __amdgpu_buffer_rsrc_t bk = buf_rsrc(kh + base, bytes), bv = buf_rsrc(vh + base, bytes);
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
-            rk[u] = pf_load16(bk, 16u * tg, 4096u * u);
-            rv[u] = pf_load16(bv, 16u * tg, 4096u * u);
+            rk[u] = buf_load16(bk, 16u * tg, 4096u * u);
+            rv[u] = buf_load16(bv, 16u * tg, 4096u * u);
         }
         word = a.mask ? a.mask[min(st, nsteps - 1)] : ~0u;
     };

@@ -656,9 +656,9 @@ int stage_create(const StageConfig* cfg, const LayerWeights* layers, int weights
         (rc = st->alloc(&st->attn, (size_t)MAX_ROWS * QD)) || (rc = st->alloc(&st->act, (size_t)MAX_ROWS * F)) ||
         (rc = st->alloc(&st->ssq, (size_t)MAX_ROWS * st->ntiles_h)) || (rc = st->alloc(&st->gpart, gpart)) ||
         (rc = st->alloc(&st->apart, (size_t)MAX_ROWS * Hq * ATTN_MAX_SPLITS * (D + 4))) ||
-        (rc = st->alloc(&st->gcnt, max_tiles)) || (rc = st->alloc(&st->acnt, (size_t)MAX_ROWS * Hkv)))
+        (rc = st->alloc(&st->gcnt, 2 * max_tiles)) || (rc = st->alloc(&st->acnt, (size_t)MAX_ROWS * Hkv)))
         return cleanup(rc);
-    if (hipMemset(st->gcnt, 0, max_tiles * sizeof(unsigned)) != hipSuccess ||
+    if (hipMemset(st->gcnt, 0, 2 * max_tiles * sizeof(unsigned)) != hipSuccess ||
         hipMemset(st->acnt, 0, (size_t)MAX_ROWS * Hkv * sizeof(unsigned)) != hipSuccess)
         return cleanup(fail(STAGE_E_HIP, "counter init failed"));
     for (int i = 0; i < META_RING; ++i)

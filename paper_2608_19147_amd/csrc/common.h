@@ -12,7 +12,14 @@ constexpr int MAX_ROWS = 64;         // activation rows per forward
 constexpr int GEMV_MAX_M = 8;        // rows one GEMV launch handles
 constexpr int GEMV_MAX_CPS = 64;     // chunks per workgroup: 4 waves x at most 16 chunks
 constexpr int ATTN_MAX_SPLITS = 64;  // KV splits per (slot, kv head)
-constexpr int ATTN_MIN_SPLIT = 256;  // fewest keys per split
+// Fewest keys per split of a request with `vectors` query vectors per kv head
+// (its tokens times the query heads of a kv head).  A workgroup with most of its
+// four tiles taken works longer per key, so its splits are shorter: 8B tree of
+// 15 nodes (60 vectors) at KV 2048 2.43 ms a step pair at 256, 2.27 at 128, 2.44
+// at 64.  Fewer vectors come in batches, whose requests fill the device: mixed
+// micro-batch of 8 3.37 ms at 256, 3.81 at 128; more are several workgroups per
+// split: 64 rows 4.69 ms at 256, 4.90 at 128.
+constexpr int attn_min_split(int vectors) { return vectors > 32 && vectors <= 64 ? 128 : 256; }
 constexpr int KGROUPS = 16;          // 16-lane key groups per attention workgroup
 
 enum Dt : int { DT_F32 = 0, DT_F16 = 1, DT_BF16 = 2 };
@@ -36,7 +43,7 @@ struct PackedMat {
 struct ReqDev {
     int P, n, S, row0, cap, mask_off, mask_len, item0;
     int rowmask_off;     // per-query-row masks [S][n][mask_len] in MetaDev::masks, or -1 (slot masks only)
-    int splits;          // most attention splits per (slot, kv head): a function of the request alone
+    int split_len;       // keys per attention split: a function of the request alone
     uint16_t* kc;        // K cache, layer 0 base: [L][S][Hkv][cap][D]
     uint16_t* vc;        // V cache
     int16_t* table;      // current beam table [S][cap] (physical slot of each row)
@@ -131,8 +138,7 @@ struct AttnArgs {
     int vector_path;         // 1: attn_kernel (vector units) instead of attn_mma_kernel
     uint16_t* bp_out; float* bc_out; int kp;   // the attention output also in prepared form (o product input, 64-row blocks)
     int dma;                 // 1: cache rows by direct loads (attn_dma_kernel) where the launch allows it: every
-                             // split at most 1024 keys, per-row masks of at most 8 KB per split, at most 256
-                             // query vectors per kv head
+                             // split at most 1024 keys, per-row masks of at most 8 KB per split
     // test support (null unless armed): the rotated queries [M][Hq][D] and the
     // scores q.k / sqrt(D) of every visible key [M][Hq][dbg_keys]
     float* dbg_q; float* dbg_logits; int dbg_keys;

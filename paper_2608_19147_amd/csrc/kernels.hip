@@ -1327,8 +1327,7 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
     const int b = it.slot;
     const int P = rq.P, n = rq.n;
     const int L = P + n;
-    int split_len = max(ATTN_MIN_SPLIT, (L + rq.splits - 1) / rq.splits);
-    split_len = (split_len + KGROUPS - 1) / KGROUPS * KGROUPS;
+    const int split_len = rq.split_len;
     const int nsplit = (L + split_len - 1) / split_len;
     if (split >= nsplit) return;
     const int j0 = split * split_len, j1 = min(L, j0 + split_len);
@@ -1540,8 +1539,7 @@ __global__ __launch_bounds__(D) void attn_merge_kernel(AttnArgs a) {
     const int m = blockIdx.x, h = blockIdx.y, d = threadIdx.x;
     const ReqDev rq = a.meta.items[a.meta.row_item[m]].rq;    // the request of row m
     const int L = rq.P + rq.n;
-    int split_len = max(ATTN_MIN_SPLIT, (L + rq.splits - 1) / rq.splits);
-    split_len = (split_len + KGROUPS - 1) / KGROUPS * KGROUPS;
+    const int split_len = rq.split_len;
     const int nsplit = (L + split_len - 1) / split_len;
     const float* pp = a.part + ((size_t)m * a.Hq + h) * a.nsplit_max * (D + 2);
     if (d < 32) {
@@ -1650,8 +1648,7 @@ __global__ __launch_bounds__(256, QTW == 1 ? 2 : 1) void attn_mma_kernel(AttnArg
     const int b = it.slot;
     const int P = rq.P, n = rq.n;
     const int L = P + n;
-    int split_len = max(ATTN_MIN_SPLIT, (L + rq.splits - 1) / rq.splits);
-    split_len = (split_len + KGROUPS - 1) / KGROUPS * KGROUPS;
+    const int split_len = rq.split_len;
     const int nsplit = (L + split_len - 1) / split_len;
     if (split >= nsplit) return;
     const int j0 = split * split_len, j1 = min(L, j0 + split_len);
@@ -2046,10 +2043,13 @@ template <int N>
 __device__ __forceinline__ void attn_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 __device__ __forceinline__ void attn_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// QTW: query tiles of 16 vectors per wave (1, 2 or 4; tile wave + 4 u); with
-// more than one, one workgroup per CU holds their registers.
-template <int D, int KVDT, int QTW, bool REC = false>
-__global__ __launch_bounds__(256, QTW == 1 ? 2 : 1) void attn_dma_kernel(AttnArgs a) {
+// A workgroup takes 64 query vectors of one (item, kv head) and one split of its
+// keys, a tile of 16 per wave; items with more are spread over blockIdx.z, whose
+// workgroups read the same rows on the same XCD (several tiles per wave spilled
+// registers and left most CUs without work: 64 rows at KV 2048 were 72
+// workgroups, 60 us).
+template <int D, int KVDT, bool REC = false>
+__global__ __launch_bounds__(256, 2) void attn_dma_kernel(AttnArgs a) {
     constexpr int HALF = D / 2;
     constexpr int NCH = D / 8;               // 16-byte chunks per cache row
     constexpr int DB = D / 32;               // k-blocks of the score products
@@ -2066,14 +2066,13 @@ __global__ __launch_bounds__(256, QTW == 1 ? 2 : 1) void attn_dma_kernel(AttnArg
     __shared__ __attribute__((aligned(16))) uint8_t smk[ATTN_SCH];
     __shared__ __attribute__((aligned(16))) uint8_t srm[ATTN_RSM];   // [row][split key] when the request has row masks
 
-    const int item = blockIdx.x, g = blockIdx.y, split = blockIdx.z;
+    const int item = blockIdx.x, g = blockIdx.y, split = blockIdx.z % a.nsplit_max, qb = blockIdx.z / a.nsplit_max;
     const ItemDev it = a.meta.items[item];
     const ReqDev rq = it.rq;
     const int b = it.slot;
     const int P = rq.P, n = rq.n;
     const int L = P + n;
-    int split_len = max(ATTN_MIN_SPLIT, (L + rq.splits - 1) / rq.splits);
-    split_len = (split_len + KGROUPS - 1) / KGROUPS * KGROUPS;
+    const int split_len = rq.split_len;
     const int nsplit = (L + split_len - 1) / split_len;
     if (split >= nsplit) return;
     const int j0 = split * split_len, j1 = min(L, j0 + split_len);
@@ -2083,7 +2082,7 @@ __global__ __launch_bounds__(256, QTW == 1 ? 2 : 1) void attn_dma_kernel(AttnArg
     const int Hq = a.Hq, Hkv = a.Hkv;
     const int gs = Hq / Hkv;
     const int R = gs * n;
-    const int nqt = (R + 15) / 16;
+    if (64 * qb >= R) return;                                // whole workgroup
     const size_t lstride = (size_t)rq.S * Hkv * rq.cap * D;
     uint16_t* kl = rq.kc + (size_t)a.layer * lstride;
     uint16_t* vl = rq.vc + (size_t)a.layer * lstride;
@@ -2142,21 +2141,20 @@ __global__ __launch_bounds__(256, QTW == 1 ? 2 : 1) void attn_dma_kernel(AttnArg
     for (int s = 0; s < ATTN_NB - 1; ++s) issue(s);
 
     // ---- this wave's query tiles: rotated, scaled, split into rounded part and residual
-    const bool active = wave < nqt;
-    u32x4 qh[QTW][DB], qr[QTW][DB];
-    int qtok[QTW];
-    float mrun[QTW], lsum[QTW];
-    f32x4_t o[QTW][MB];
-#pragma unroll
-    for (int u = 0; u < QTW; ++u) {
-        const int r = 16 * (wave + 4 * u) + ql;
-        const bool ok = wave + 4 * u < nqt && r < R;
+    const int r = 64 * qb + 16 * wave + ql;                  // this lane's query vector
+    const bool active = 64 * qb + 16 * wave < R;
+    u32x4 qh[DB], qr[DB];
+    int qtok;
+    float mrun, lsum;
+    f32x4_t o[MB];
+    {
+        const bool ok = r < R;
         const int i = ok ? r / gs : 0, h = g * gs + (ok ? r % gs : 0);
         const int m = rowbase + i;
         const float* qrow = a.qkv + (size_t)m * a.qkv_ld + (size_t)h * D;
-        qtok[u] = ok ? i : n;
-        mrun[u] = -INFINITY;
-        lsum[u] = 0.f;
+        qtok = ok ? i : n;
+        mrun = -INFINITY;
+        lsum = 0.f;
         // every load of the tile at once (row 0 of the item stands in for a missing
         // row): q and its rotary partners, then (cos, sin) at the row's position
         float4 qa[DB][2], qp[DB][2], rc[DB][4];
@@ -2207,12 +2205,12 @@ __global__ __launch_bounds__(256, QTW == 1 ? 2 : 1) void attn_dma_kernel(AttnArg
             }
 #pragma unroll
             for (int w2 = 0; w2 < 4; ++w2) {
-                qh[u][ib][w2] = (uint32_t)hb[2 * w2] | ((uint32_t)hb[2 * w2 + 1] << 16);
-                qr[u][ib][w2] = (uint32_t)rb[2 * w2] | ((uint32_t)rb[2 * w2 + 1] << 16);
+                qh[ib][w2] = (uint32_t)hb[2 * w2] | ((uint32_t)hb[2 * w2 + 1] << 16);
+                qr[ib][w2] = (uint32_t)rb[2 * w2] | ((uint32_t)rb[2 * w2 + 1] << 16);
             }
         }
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) o[u][mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int mb = 0; mb < MB; ++mb) o[mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
 
     for (int st = 0; st < nsteps; ++st) {
@@ -2252,11 +2250,12 @@ __global__ __launch_bounds__(256, QTW == 1 ? 2 : 1) void attn_dma_kernel(AttnArg
                     kk[w2] = (uint32_t)kb8[2 * w2] | ((uint32_t)kb8[2 * w2 + 1] << 16);
                     vv[w2] = (uint32_t)vb8[2 * w2] | ((uint32_t)vb8[2 * w2 + 1] << 16);
                 }
-                // append: owner of row j writes it
-                const size_t off = (((size_t)b * Hkv + g) * rq.cap + j) * D + 8 * c;
-                *(u32x4*)(kl + off) = kk;
-                *(u32x4*)(vl + off) = vv;
-                if (a.layer == 0 && g == 0 && c == 0) rq.table[(size_t)b * rq.cap + j] = (int16_t)b;
+                if (qb == 0) {                               // append: owner of row j writes it
+                    const size_t off = (((size_t)b * Hkv + g) * rq.cap + j) * D + 8 * c;
+                    *(u32x4*)(kl + off) = kk;
+                    *(u32x4*)(vl + off) = vv;
+                    if (a.layer == 0 && g == 0 && c == 0) rq.table[(size_t)b * rq.cap + j] = (int16_t)b;
+                }
                 if (smk[x0 + k] != 0) {                      // a kept row enters; a dropped one stays zero
                     const int pos16 = 16 * (c ^ (k % NCH));
                     *(u32x4*)(kb + k * RB + pos16) = kk;
@@ -2306,12 +2305,10 @@ __global__ __launch_bounds__(256, QTW == 1 ? 2 : 1) void attn_dma_kernel(AttnArg
                 const uint32_t byte = ((e < 4 ? w0 : w1) >> (8 * (e & 3))) & 0xFFu;
                 vb0 |= ((kbase + ko < j1 && byte != 0u) ? 1u : 0u) << e;
             }
-#pragma unroll
-            for (int u = 0; u < QTW; ++u) {
-                if (wave + 4 * u >= nqt) continue;           // wave-uniform
+            {
                 uint32_t vbits = vb0;
                 if (rmask) {                                 // this query row's own mask bytes (uniform branch)
-                    const uint32_t ra = (uint32_t)(uintptr_t)srm + (uint32_t)(min(qtok[u], n - 1) * rspan + x0 + 4 * lg);
+                    const uint32_t ra = (uint32_t)(uintptr_t)srm + (uint32_t)(min(qtok, n - 1) * rspan + x0 + 4 * lg);
                     uint32_t r0 = attn_lds4(ra), r1 = attn_lds4(ra + 16);
                     attn_lgkm();
                     touch_u(r0);
@@ -2323,12 +2320,12 @@ __global__ __launch_bounds__(256, QTW == 1 ? 2 : 1) void attn_dma_kernel(AttnArg
                 f32x4_t s0 = f32x4_t{0.f, 0.f, 0.f, 0.f}, s1 = s0;
 #pragma unroll
                 for (int ib = 0; ib < DB; ++ib) {
-                    s0 = mma_kv<KVDT>(kf0[ib], qh[u][ib], s0);
-                    s1 = mma_kv<KVDT>(kf1[ib], qh[u][ib], s1);
-                    s0 = mma_kv<KVDT>(kf0[ib], qr[u][ib], s0);
-                    s1 = mma_kv<KVDT>(kf1[ib], qr[u][ib], s1);
+                    s0 = mma_kv<KVDT>(kf0[ib], qh[ib], s0);
+                    s1 = mma_kv<KVDT>(kf1[ib], qh[ib], s1);
+                    s0 = mma_kv<KVDT>(kf0[ib], qr[ib], s0);
+                    s1 = mma_kv<KVDT>(kf1[ib], qr[ib], s1);
                 }
-                const int last = P + qtok[u] - kbase;        // keys up to kbase + last are causal
+                const int last = P + qtok - kbase;        // keys up to kbase + last are causal
                 float sv[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
@@ -2337,7 +2334,6 @@ __global__ __launch_bounds__(256, QTW == 1 ? 2 : 1) void attn_dma_kernel(AttnArg
                     sv[e] = (((vbits >> e) & 1u) && ko <= last) ? x : -INFINITY;
                 }
                 if constexpr (REC) {                         // test support: this tile's visible scores
-                    const int r = 16 * (wave + 4 * u) + ql;
                     if (r < R) {
                         const size_t row = ((size_t)(rowbase + r / gs) * Hq + g * gs + r % gs) * a.dbg_keys;
 #pragma unroll
@@ -2355,18 +2351,18 @@ __global__ __launch_bounds__(256, QTW == 1 ? 2 : 1) void attn_dma_kernel(AttnArg
                 mx = fmaxf(x0f, x1f);
                 lane_pair_k(mx, 32, x0f, x1f);
                 mx = fmaxf(x0f, x1f);
-                const float mn = fmaxf(mrun[u], mx);
+                const float mn = fmaxf(mrun, mx);
                 // no key seen yet (mn = -inf): base 0 makes every term and the correction 0
                 const float base = mn == -INFINITY ? 0.f : mn;
-                const float corr = __builtin_amdgcn_exp2f(mrun[u] - base);
+                const float corr = __builtin_amdgcn_exp2f(mrun - base);
                 float pv[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) pv[e] = __builtin_amdgcn_exp2f(sv[e] - base);
                 float ps = 0.f;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) ps += pv[e];
-                lsum[u] = lsum[u] * corr + ps;
-                mrun[u] = mn;
+                lsum = lsum * corr + ps;
+                mrun = mn;
                 u32x4 pb;
 #pragma unroll
                 for (int w2 = 0; w2 < 4; ++w2) pb[w2] = kv_pack2<KVDT>(pv[2 * w2], pv[2 * w2 + 1]);
@@ -2374,25 +2370,22 @@ __global__ __launch_bounds__(256, QTW == 1 ? 2 : 1) void attn_dma_kernel(AttnArg
 #pragma unroll
                     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                        for (int jj = 0; jj < 4; ++jj) o[u][mb][jj] *= corr;
+                        for (int jj = 0; jj < 4; ++jj) o[mb][jj] *= corr;
                 }
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb) o[u][mb] = mma_kv<KVDT>(vf[mb], pb, o[u][mb]);
+                for (int mb = 0; mb < MB; ++mb) o[mb] = mma_kv<KVDT>(vf[mb], pb, o[mb]);
             }
         }
     }
     attn_vm<0>();                                            // no direct load may land after the workgroup ends
 
     // ---- this split's partial of each query vector: (max, sum, unnormalized output)
-#pragma unroll
-    for (int u = 0; u < QTW; ++u) {
-        if (wave + 4 * u >= nqt) continue;
-        float x0f, x1f, lt = lsum[u];
+    if (active) {
+        float x0f, x1f, lt = lsum;
         lane_pair_k(lt, 16, x0f, x1f);
         lt = x0f + x1f;
         lane_pair_k(lt, 32, x0f, x1f);
         lt = x0f + x1f;
-        const int r = 16 * (wave + 4 * u) + ql;
         if (r < R) {
             const int i = r / gs, h = g * gs + (r % gs);
             const int m = rowbase + i;
@@ -2400,9 +2393,9 @@ __global__ __launch_bounds__(256, QTW == 1 ? 2 : 1) void attn_dma_kernel(AttnArg
             // 16-byte stores (the record is only 8-byte aligned; the hardware takes
             // 4-byte aligned wide stores): a store per value lengthens the launch's drain
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) __builtin_memcpy(pp + 2 + 16 * mb + 4 * lg, &o[u][mb], 16);
+            for (int mb = 0; mb < MB; ++mb) __builtin_memcpy(pp + 2 + 16 * mb + 4 * lg, &o[mb], 16);
             if (lg == 0) {
-                const float2 ml = {mrun[u], lt};
+                const float2 ml = {mrun, lt};
                 __builtin_memcpy(pp, &ml, 8);
             }
         }
@@ -2415,18 +2408,11 @@ hipError_t launch_attention(const AttnArgs& a, int head_dim, int queries_per_ite
     const bool wide = queries_per_item_max > 4;
     const bool bf = a.kv_dt == DT_BF16;
     const bool one = queries_per_item_max <= 64;                // every item's query tiles: one per wave
-    // the direct-load form takes up to four tiles per wave (256 query vectors per kv head)
-    const int dq = !a.dma || queries_per_item_max > 256 ? 0 : one ? 1 : queries_per_item_max <= 128 ? 2 : 4;
-#define ATTN_DMA_Q(D_, T_, R_)                                                                    \
-    do {                                                                                          \
-        if (bf) attn_dma_kernel<D_, DT_BF16, T_, R_><<<grid, block, 0, st>>>(a);                  \
-        else attn_dma_kernel<D_, DT_F16, T_, R_><<<grid, block, 0, st>>>(a);                      \
-    } while (0)
+    const dim3 dgrid(a.meta.n_items, a.Hkv, a.nsplit_max * (unsigned)((queries_per_item_max + 63) / 64));
 #define ATTN_MMA_R(D_, R_)                                                                        \
     do {                                                                                          \
-        if (dq == 1) ATTN_DMA_Q(D_, 1, R_);                                                       \
-        else if (dq == 2) ATTN_DMA_Q(D_, 2, R_);                                                  \
-        else if (dq == 4) ATTN_DMA_Q(D_, 4, R_);                                                  \
+        if (a.dma && bf) attn_dma_kernel<D_, DT_BF16, R_><<<dgrid, block, 0, st>>>(a);            \
+        else if (a.dma) attn_dma_kernel<D_, DT_F16, R_><<<dgrid, block, 0, st>>>(a);              \
         else if (bf && one) attn_mma_kernel<D_, DT_BF16, 1, R_><<<grid, block, 0, st>>>(a);       \
         else if (bf) attn_mma_kernel<D_, DT_BF16, 2, R_><<<grid, block, 0, st>>>(a);              \
         else if (one) attn_mma_kernel<D_, DT_F16, 1, R_><<<grid, block, 0, st>>>(a);              \
@@ -2452,7 +2438,6 @@ hipError_t launch_attention(const AttnArgs& a, int head_dim, int queries_per_ite
     }
 #undef ATTN_MMA
 #undef ATTN_MMA_R
-#undef ATTN_DMA_Q
     return hipGetLastError();
 }
 

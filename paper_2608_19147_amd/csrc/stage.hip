@@ -1736,13 +1736,14 @@ int stage_forward(Stage* st, const StageRequest* reqs, int n_req, const void* hi
             // attention splits: about two workgroups per CU over the request's own
             // slots and kv heads (never its batch-mates, so they cannot change its
             // result), at most ATTN_MAX_SPLITS
-            d.splits = std::max(1, std::min(ATTN_MAX_SPLITS, 2 * st->n_cus / (S * Hkv)));
-            if (const char* e = std::getenv("STAGE_ATTN_SPLITS")) d.splits = std::max(1, std::min(ATTN_MAX_SPLITS, atoi(e)));
-            max_splits = std::max(max_splits, d.splits);
+            int splits = std::max(1, std::min(ATTN_MAX_SPLITS, 2 * st->n_cus / (S * Hkv)));
+            if (const char* e = std::getenv("STAGE_ATTN_SPLITS")) splits = std::max(1, std::min(ATTN_MAX_SPLITS, atoi(e)));
             {                                            // the direct-load attention stages a whole split's table
                 const int Lr = d.P + n;
-                int sl = std::max(ATTN_MIN_SPLIT, (Lr + d.splits - 1) / d.splits);
+                int sl = std::max(attn_min_split(gs * n), (Lr + splits - 1) / splits);
                 sl = (sl + KGROUPS - 1) / KGROUPS * KGROUPS;
+                d.split_len = sl;
+                max_splits = std::max(max_splits, (Lr + sl - 1) / sl);
                 // and addresses one layer of the cache through a buffer resource (32-bit offsets)
                 const size_t layer_bytes = (size_t)S * Hkv * kv->cap * c.head_dim * 2;
                 // and the split's rows of a per-query-row mask (n rows x split keys, at most 8 KB)
@@ -1986,7 +1987,7 @@ int stage_forward(Stage* st, const StageRequest* reqs, int n_req, const void* hi
             a.part = st->apart;
             a.counters = st->acnt;
             // splits per (slot, kv head) follow the request's own length and slot count
-            // only (at least ATTN_MIN_SPLIT keys each, at most its `splits`), so
+            // only (its split_len), so
             // batch-mates never change a request's result; nsplit_max bounds the grid
             // and is the stride of the partials
             a.nsplit_max = max_splits;

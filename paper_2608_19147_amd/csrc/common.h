@@ -86,6 +86,8 @@ struct GemvArgs {
     const float* cb_in;                            // norm 1: scale c each row was prepared with
     int norm;                                      // 0: none, 1: deferred RMSNorm (factor rs / c), 2: prepared normalized
     int kp, kg;                                    // prepared row stride; groups of 128 k per wave
+    int pt;                                        // weight tiles per workgroup: 1, or 2 that share the prepared rows
+    int pair_rot;                                  // the matrix may run with pt = 2: groups rotate by the pair's index
     float* rs_out;                                 // norm 1: rs of each row, for the next residual product
     uint16_t* bp_out; float* bc_out; float* cb_out;  // RESID / SWIGLU: the next product's input
     const uint16_t* gamma_next; int gamma_next_dt; // RESID: RMSNorm weight of the next product

@@ -438,15 +438,29 @@ __device__ __forceinline__ float wave_sum_all(float v) {
 }
 
 // Largest value / smallest integer over the wave, identical in every lane.
+// (lane exchanges within the vector unit; through LDS each of the six took a round trip).
 __device__ __forceinline__ float wave_max_all(float v) {
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
+    v = fmaxf(v, dpp_f<0xB1>(v));
+    v = fmaxf(v, dpp_f<0x4E>(v));
+    v = fmaxf(v, dpp_f<0x141>(v));
+    v = fmaxf(v, dpp_f<0x140>(v));
+    uint32_t u = __float_as_uint(v);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    u = __float_as_uint(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+    const auto q = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
 }
+template <int CTRL>
+__device__ __forceinline__ int dpp_i(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false); }
 __device__ __forceinline__ int wave_min_all(int v) {
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) v = min(v, __shfl_xor(v, o, 64));
-    return v;
+    v = min(v, dpp_i<0xB1>(v));
+    v = min(v, dpp_i<0x4E>(v));
+    v = min(v, dpp_i<0x141>(v));
+    v = min(v, dpp_i<0x140>(v));
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = min((int)r[0], (int)r[1]);
+    const auto q = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return min((int)q[0], (int)q[1]);
 }
 
 // Sum over aligned groups of 32 lanes, identical in every lane of the group.
@@ -566,7 +580,7 @@ __device__ __forceinline__ void row_factors_finish(const GemvArgs& a, int K, boo
     }
     ss += dpp_f<0xB1>(ss);                                    // lane ^ 1
     ss += dpp_f<0x4E>(ss);                                    // lane ^ 2: the row's 4 parts
-    if (part == 0) {
+    if (part == 0 && m < 64) {                                // (a 512-thread workgroup's upper half has no row)
         float f = 1.f;
         if (a.norm == 1 && m < a.M) {
             const float rs = rsqrtf(ss / (float)K + a.eps);
@@ -599,20 +613,33 @@ __device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t o
 // with -1.  That leaves one multiply-add per result and group.
 // Z = 2: 33..64 rows, as two workgroups of 32 rows per tile that run one after
 // the other on one XCD (the second finds the codes in its L2).
-template <int NCB, int Z>
-__global__ __launch_bounds__(256, 2) void gemm_bp_kernel(GemvArgs a) {
+// PT = 2: eight waves take two tiles; the two waves of a K range fetch half of
+// its prepared rows each and share them through LDS.  With every wave fetching
+// its own, the caches delivered about 9.5 TB/s and bound the product: the LM
+// head (20 rows, 8 KB of rows per 4 KB of codes) streamed its codes at 3.1 TB/s,
+// at 16 rows (4 KB) 4.3.
+template <int NCB, int Z, int PT>
+__global__ __launch_bounds__(256 * PT, 2) void gemm_bp_kernel(GemvArgs a) {
     constexpr int MP = 16 * NCB;
     constexpr int NV = MP * 64 / 256;
-    __shared__ float red[4][MP][65];
+    // the shared rows [buffer][K range][fragment][lane] (PT = 2) and, after the
+    // products, the waves' sums [tile][wave][row][65]
+    constexpr int SBB = PT == 2 ? 2 * 4 * 4 * NCB * 1024 : 0, REDB = PT * 4 * MP * 65 * 4;
+    __shared__ __attribute__((aligned(16))) uint8_t raw[SBB > REDB ? SBB : REDB];
     __shared__ float fs[64];
-    __shared__ float sres[NCB >= 2 ? MP : 1][64], sgam[64], srs[NCB >= 2 ? MP : 1];   // residual-epilogue inputs read at the start
+    __shared__ float sres_[PT][NCB >= 2 ? MP : 1][64], sgam_[PT][64], srs_[PT][NCB >= 2 ? MP : 1];   // residual-epilogue inputs read at the start
     __shared__ int last_s;
-    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: scalar loop control
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = wave & 3;   // uniform: scalar loop control
+    const int tl = wave >> 2, tid = threadIdx.x & 255, lane = tid & 63;   // tile of the workgroup, thread of the tile
     const int l16 = lane & 15, lg = lane >> 4;
-    const int t = Z == 1 ? (int)blockIdx.x : (int)((blockIdx.x >> 4) * 8 + (blockIdx.x & 7)), s = blockIdx.y;
+    const int wg = Z == 1 ? (int)blockIdx.x : (int)((blockIdx.x >> 4) * 8 + (blockIdx.x & 7)), s = blockIdx.y;
     const int m0 = Z == 1 ? 0 : 32 * ((blockIdx.x >> 3) & 1);   // first row
     const PackedMat W = a.W;
-    if (Z > 1 && t >= W.ntiles) return;                         // whole workgroup
+    if (Z > 1 && PT * wg >= W.ntiles) return;                   // whole workgroup
+    const bool has = PT * wg + tl < W.ntiles;
+    const int t = has ? PT * wg + tl : W.ntiles - 1;            // an odd matrix's missing tile repeats the last; its results are dropped
+    float (*red)[MP][65] = (float (*)[MP][65])(raw + (size_t)tl * 4 * MP * 65 * 4);
+    float (*sres)[64] = sres_[tl], *sgam = sgam_[tl], *srs = srs_[tl];
     const int M = a.M, K = W.k;
     const int g0 = (4 * s + w) * a.kg, g1 = min(W.ngroups, g0 + a.kg);
     uint32_t magic = 0x64006400u;
@@ -630,6 +657,11 @@ __global__ __launch_bounds__(256, 2) void gemm_bp_kernel(GemvArgs a) {
             sv[rt] = __builtin_amdgcn_raw_buffer_load_b16(rsc, so, 128 * gi + 32 * rt, 0);
         }
     };
+    auto ldc = [&](int gi, float (&cv)[NCB]) {
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb)
+            cv[cb] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rc, co, 1024 * gi + 256 * cb, 0));
+    };
     // prepared operand and corrections (row l16, chunk lg) of one group as stored;
     // entries at k >= K (past the end of a ragged last group) are dropped when the
     // group computes, so nothing waits for these loads before then
@@ -638,8 +670,8 @@ __global__ __launch_bounds__(256, 2) void gemm_bp_kernel(GemvArgs a) {
         for (int cb = 0; cb < NCB; ++cb) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) bv[cb][i] = buf_load16<0>(rb, bo, 16384 * gi + 4096 * cb + 1024 * i);
-            cv[cb] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rc, co, 1024 * gi + 256 * cb, 0));
         }
+        ldc(gi, cv);
     };
 
     f32x4_t acc[4][NCB];
@@ -657,6 +689,20 @@ __global__ __launch_bounds__(256, 2) void gemm_bp_kernel(GemvArgs a) {
     u32x4 wr[2][4], br[2][NCB][4];
     uint16_t sr[2][4];
     float cr[2][NCB];
+    // PT = 2: this wave's half of the rows of its K range
+    u32x4 rh[2 * NCB];
+    u32x4 (*sb)[4][4 * NCB][64] = (u32x4 (*)[4][4 * NCB][64])raw;
+    auto ldh = [&](int gi) {
+#pragma unroll
+        for (int u = 0; u < 2 * NCB; ++u) {
+            const int f = 2 * NCB * tl + u;
+            rh[u] = buf_load16<0>(rb, bo, 16384 * gi + 1024 * f);
+        }
+    };
+    auto puth = [&](int buf) {
+#pragma unroll
+        for (int u = 0; u < 2 * NCB; ++u) sb[buf][w][2 * NCB * tl + u][lane] = rh[u];
+    };
     auto compute = [&](int gi, const u32x4 (&wv)[4], const uint16_t (&sv)[4], u32x4 (&bv)[NCB][4], float (&cv)[NCB]) {
         const int kb = 128 * gi;
         if (kb + 128 > K) {                              // a ragged last group (uniform)
@@ -701,9 +747,11 @@ __global__ __launch_bounds__(256, 2) void gemm_bp_kernel(GemvArgs a) {
                 for (int j = 0; j < 4; ++j) acc[rt][cb][j] = __builtin_fmaf(scl, c[cb][j], acc[rt][cb][j]);
         }
     };
-    // each tile starts its range at its own group (rotation by the tile index): at
+    // each tile starts its range at its own group (rotation by the tile's index, in
+    // a matrix that may run in pairs by the pair's, for either PT: the order of the
+    // sums, and with it the result, must not depend on the form): at
     // any moment the workgroups read different parts of the prepared operand
-    const int n = g1 - g0, rot = __builtin_amdgcn_readfirstlane(n > 0 ? t % n : 0);
+    const int n = g1 - g0, rot = __builtin_amdgcn_readfirstlane(n > 0 ? (a.pair_rot ? t >> 1 : t) % n : 0);
     auto G = [&](int q) {
         q = min(q, n - 1) + rot;
         return g0 + (q >= n ? q - n : q);
@@ -738,7 +786,11 @@ __global__ __launch_bounds__(256, 2) void gemm_bp_kernel(GemvArgs a) {
     __builtin_amdgcn_sched_barrier(0);
     if (n > 0) {
         ldw(G(0), wr[0], sr[0]);
-        ldb(G(0), br[0], cr[0]);
+        if constexpr (PT == 1) ldb(G(0), br[0], cr[0]);
+        else {
+            ldc(G(0), cr[0]);
+            ldh(G(0));
+        }
     }
     __builtin_amdgcn_sched_barrier(0);
     row_factors_finish(a, K, t == 0 && s == 0, rfl, fs);
@@ -753,7 +805,33 @@ __global__ __launch_bounds__(256, 2) void gemm_bp_kernel(GemvArgs a) {
             if (tid < MP) srs[tid] = prs;
         }
     }
-    if (n > 0) {
+    if constexpr (PT == 2) {
+        // step q: the K range's rows of group q are in LDS buffer q & 1; every wave
+        // takes kg steps (the barriers), those past its range without products
+        if (n > 0) {
+            puth(0);
+            ldh(G(1));
+        }
+        auto step = [&](int q, u32x4 (&wv)[4], uint16_t (&sv)[4], float (&cv)[NCB], u32x4 (&wn)[4], uint16_t (&sn)[4], float (&cn)[NCB]) {
+            __syncthreads();
+            if (q >= n) return;                          // uniform in the wave
+            ldw(G(q + 1), wn, sn);
+            ldc(G(q + 1), cn);
+            puth((q + 1) & 1);
+            ldh(G(q + 2));
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) br[0][cb][i] = sb[q & 1][w][4 * cb + i][lane];
+            compute(G(q), wv, sv, br[0], cv);
+        };
+        for (int q = 0; q < a.kg; q += 2) {
+            step(q, wr[0], sr[0], cr[0], wr[1], sr[1], cr[1]);
+            if (q + 1 < a.kg) step(q + 1, wr[1], sr[1], cr[1], wr[0], sr[0], cr[0]);
+        }
+        __syncthreads();                                 // the rows in LDS give way to the sums
+    } else if (n > 0) {
         // group q computes from set q & 1 while group q + 1 loads into the other set:
         // whole pairs of groups, then a last single group
         int q = 0;
@@ -795,10 +873,10 @@ __global__ __launch_bounds__(256, 2) void gemm_bp_kernel(GemvArgs a) {
 #pragma unroll
         for (int q = 0; q < NV; ++q) {
             const int idx = tid + 256 * q;
-            if (m0 + (idx >> 6) < M)
+            if (has && m0 + (idx >> 6) < M)
                 store_coherent(&a.partial[((size_t)s * M + m0 + (idx >> 6)) * ldp + t * 64 + (idx & 63)], vals[q]);
         }
-        if (!last_arrival(&a.counters[Z == 1 ? t : 2 * t + (m0 >> 5)], (unsigned)a.ksplit, &last_s)) return;
+        if (!last_arrival(&a.counters[Z == 1 ? wg : 2 * wg + (m0 >> 5)], (unsigned)a.ksplit, &last_s)) return;
         const size_t stride = (size_t)M * ldp;
 #pragma unroll
         for (int q = 0; q < NV; ++q) vals[q] = 0.f;
@@ -819,12 +897,13 @@ __global__ __launch_bounds__(256, 2) void gemm_bp_kernel(GemvArgs a) {
         }
     }
 
-    // ---- epilogue
+    // ---- epilogue (row limit 0 for a missing tile: its threads only take part in the barriers and sums)
+    const int Mt = has ? M : 0;
     if (a.epi == EPI_STORE) {
 #pragma unroll
         for (int q = 0; q < NV; ++q) {
             const int idx = tid + 256 * q;
-            if (m0 + (idx >> 6) < M) {
+            if (m0 + (idx >> 6) < Mt) {
                 const int m = m0 + (idx >> 6), n = t * 64 + (idx & 63);
                 if (n < W.n) a.out[(size_t)m * a.out_ld + n] = vals[q] * fs[m];
             }
@@ -852,7 +931,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bp_kernel(GemvArgs a) {
             const int idx = tid + 256 * q;
             const int m = m0 + (idx >> 6), r = idx & 63;              // one row per wave: whole waves take part
             const int n = t * 64 + r;
-            const bool ok = m < M && n < W.n;
+            const bool ok = m < Mt && n < W.n;
             float xn = 0.f;
             if (ok) {
                 float xr;
@@ -864,8 +943,8 @@ __global__ __launch_bounds__(256, 2) void gemm_bp_kernel(GemvArgs a) {
             }
             // the row's sum of squares over the tile: row m is this wave's 64 lanes
             const float ss = wave_sum_all(xn * xn);
-            if (a.ssq_out && m < M && r == 0) a.ssq_out[(size_t)m * W.ntiles + t] = ss;
-            if (a.bp_out && m < M) {                                    // the next product's input
+            if (a.ssq_out && m < Mt && r == 0) a.ssq_out[(size_t)m * W.ntiles + t] = ss;
+            if (a.bp_out && m < Mt) {                                    // the next product's input
                 float c, gm;
                 if constexpr (PRE) {
                     c = srs[m - m0];
@@ -886,14 +965,15 @@ __global__ __launch_bounds__(256, 2) void gemm_bp_kernel(GemvArgs a) {
         for (int q = 0; q < NV; ++q) {
             const int idx = tid + 256 * q;
             const int m = m0 + (idx >> 6), r = idx & 63;
+            if (m >= Mt) continue;                                     // uniform in the wave
             const int n = t * 64 + r;
-            const bool ok = m < M && n < W.n;
+            const bool ok = n < W.n;
             const float v = ok ? vals[q] * fs[m] : -INFINITY;
             if (ok && a.out) a.out[(size_t)m * a.out_ld + n] = v;
             const float mx = wave_max_all(v);
             const int arg = wave_min_all((ok && v == mx) ? n : INT_MAX);
             const float se = wave_sum_all(ok ? expf(v - mx) : 0.f);
-            if (m < M && r == 0) a.top1_part[(size_t)m * W.ntiles + t] = make_float4(mx, __int_as_float(arg), se, 0.f);
+            if (r == 0) a.top1_part[(size_t)m * W.ntiles + t] = make_float4(mx, __int_as_float(arg), se, 0.f);
         }
     } else {  // EPI_SWIGLU: rows 0..31 of the tile are gate rows, 32..63 the matching up rows
 #pragma unroll
@@ -906,24 +986,32 @@ __global__ __launch_bounds__(256, 2) void gemm_bp_kernel(GemvArgs a) {
             const int idx = i0 + tid;
             const int ml = idx >> 5, m = m0 + ml, r = idx & 31;
             const int f = t * 32 + r;
-            const bool ok = m < M && f < a.n_valid;
+            const bool ok = m < Mt && f < a.n_valid;
             float y = 0.f;
             if (ok) {
                 const float gt = red[0][ml][r], up = red[0][ml][r + 32];
                 y = (gt / (1.0f + expf(-gt))) * up;
                 a.out[(size_t)m * a.out_ld + f] = y;
             }
-            if (a.bp_out && m < M) bp_put(a.bp_out, a.bc_out, a.kp, m, f, y, ok);
+            if (a.bp_out && m < Mt) bp_put(a.bp_out, a.bc_out, a.kp, m, f, y, ok);
         }
     }
 }
 
 hipError_t launch_gemm_bp(const GemvArgs& a, hipStream_t st) {
     if (a.M < 1 || a.M > 64 || a.W.gchunks != 4 || a.kg < 1 || a.kp % 128) return hipErrorInvalidValue;
-    const dim3 grid(a.W.ntiles, a.ksplit), block(256);
-    if (a.M <= 16) gemm_bp_kernel<1, 1><<<grid, block, 0, st>>>(a);
-    else if (a.M <= 32) gemm_bp_kernel<2, 1><<<grid, block, 0, st>>>(a);
-    else gemm_bp_kernel<2, 2><<<dim3((a.W.ntiles + 7) / 8 * 16, a.ksplit), block, 0, st>>>(a);
+    if (a.pt != 1 && a.pt != 2) return hipErrorInvalidValue;
+    const int wgs = (a.W.ntiles + a.pt - 1) / a.pt;
+    const dim3 grid(wgs, a.ksplit), zgrid((wgs + 7) / 8 * 16, a.ksplit), block(256 * a.pt);
+    if (a.pt == 1) {
+        if (a.M <= 16) gemm_bp_kernel<1, 1, 1><<<grid, block, 0, st>>>(a);
+        else if (a.M <= 32) gemm_bp_kernel<2, 1, 1><<<grid, block, 0, st>>>(a);
+        else gemm_bp_kernel<2, 2, 1><<<zgrid, block, 0, st>>>(a);
+    } else {
+        if (a.M <= 16) gemm_bp_kernel<1, 1, 2><<<grid, block, 0, st>>>(a);
+        else if (a.M <= 32) gemm_bp_kernel<2, 1, 2><<<grid, block, 0, st>>>(a);
+        else gemm_bp_kernel<2, 2, 2><<<zgrid, block, 0, st>>>(a);
+    }
     return hipGetLastError();
 }
 

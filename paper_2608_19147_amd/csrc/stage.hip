@@ -100,6 +100,21 @@ void pf_plan(int tiles, int ng, int n_cus, int& splits, int& kg) {
     }
 }
 
+// Whether a prepared-operand product may take two weight tiles per workgroup,
+// which share the prepared rows, and whether M rows do: more than 16 (the rows
+// then outweigh the codes), with pairs enough to give most CUs a workgroup and 4
+// to 8 groups per wave (fewer do not repay the barriers; a pair's common rotation
+// costs the long ranges of 70B gate|up 3% at one row).  gate|up of the 8B stage
+// (224 pairs of 8 groups): 20 rows 23.4 -> 20.1 us, 64 rows 46 -> 41.
+bool bp_pairable(const DevMat& m, int n_cus) {
+    const long pairs = (long)(m.pm.ntiles + 1) / 2 * m.bp_split;
+    return m.bp_kg >= 4 && m.bp_kg <= 8 && 4 * pairs >= 3L * n_cus;
+}
+void bp_form(GemvArgs& a, const DevMat& m, int M, int n_cus) {
+    a.pair_rot = bp_pairable(m, n_cus);
+    a.pt = a.pair_rot && M > 16 ? 2 : 1;
+}
+
 struct LayerDev {
     DevMat qkv, o, gu, d;
     uint16_t* attn_norm = nullptr;
@@ -1313,6 +1328,7 @@ int stage_head_top1(Stage* st, const void* hidden, int M, int32_t* token_out, fl
     a.M = M;
     a.kp = st->kp;
     a.kg = st->head.bp_kg;
+    bp_form(a, st->head, M, st->n_cus);
     a.ksplit = 1;
     a.partial = st->gpart;
     a.counters = st->gcnt;
@@ -1926,6 +1942,7 @@ int stage_forward(Stage* st, const StageRequest* reqs, int n_req, const void* hi
         a.counters = st->gcnt;
         a.ksplit = m.bp_split;
         a.kg = m.bp_kg;
+        bp_form(a, m, M, st->n_cus);
         return launch_gemm_bp(a, s);
     };
 

@@ -1,0 +1,63 @@
+"""Edges of the prompt and product kernels against the oracle and each other:
+prompt lengths around the 64-token block, the 8-block band and the split of K
+(tiny stage, FFN 688: a ragged last group of k), past rows with masked holes at
+lengths around the attention's 32-key step and 64-query block; a row's result in
+a forward must be bitwise the same whichever product form its batch selects (16
+rows or fewer, 17-32, 33-64).
+
+Tolerance: TOL_STAGE, the stage tolerance every parity test uses (fp16 product
+inputs and 16-bit cache rows; 2.8e-3 measured on these paths)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from gpu_cases import TOL_STAGE, Pair, full_mask, host, rel_err, req, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+TINY2 = synth.with_layers(synth.TINY, 2)
+
+
+@pytest.fixture(scope="module")
+def tiny():
+    p = Pair(TINY2, 410)
+    yield p
+    p.close()
+
+
+@pytest.mark.parametrize("P0,n,holes", [(0, 17, 0), (0, 128, 0), (0, 129, 0), (31, 33, 0.2), (32, 63, 0.2), (33, 64, 0.2),
+                                        (65, 200, 0.1), (1, 520, 0)])
+def test_prompt_edges(tiny, P0, n, holes):
+    g, o = tiny.states(1, P0, P0 + n + 8, 411 + n)
+    past = np.ones(P0, np.uint8)
+    if holes:
+        past = synth.hole_mask(P0, holes, 411 + n, 0)
+        past[0] = 1
+    x = synth.make_hidden(TINY2, n, 411 + n, 1)
+    pos = int(past.sum()) + np.arange(n)
+    out = host(tiny.gpu.prefill(g, pos, x.cuda(), past if holes else None))
+    ref = oracle.forward(tiny.orc, o, host(x), pos[None], None, np.concatenate([past, np.ones(n, np.uint8)])[None])
+    assert rel_err(out, ref) <= TOL_STAGE
+    for l in range(TINY2.n_layers):
+        k, v = g.read(l, 0, P0, n)
+        assert rel_err(host(k), o.K[l][0][:, P0:P0 + n]) <= TOL_STAGE
+        assert rel_err(host(v), o.V[l][0][:, P0:P0 + n]) <= TOL_STAGE
+    g.free()
+
+
+def test_row_result_does_not_depend_on_the_product_form():
+    """One 8B layer: a 5-token request alone (one tile per workgroup), with 15 more
+    rows (gate|up in pairs) and with 55 more (two 32-row workgroups per tile)."""
+    p = Pair(synth.with_layers(synth.LLAMA8B_HALF, 1), 420)
+    x = synth.make_hidden(p.shape, 60, 420)
+    outs = []
+    for others in ((), (15,), (55,)):
+        states = [p.states(1, 40, 120, 420, stream=r, with_oracle=False)[0] for r in range(1 + len(others))]
+        reqs = [req(s, (40 + np.arange(n))[None], full_mask(1, 40 + n)) for s, n in zip(states, (5,) + others)]
+        outs.append(run_gpu(p, reqs, x[:5 + sum(others)])[:5].copy())
+        for s in states:
+            s.free()
+    assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
+    p.close()

@@ -1039,7 +1039,8 @@ __device__ __forceinline__ void load8(const void* p, int dt, size_t i, float (&v
 // One wave per row, eight rows per workgroup (the eight 16-byte pieces a 128-byte
 // line of a block takes come from one workgroup), eight consecutive k per lane
 // and step; the row stays in registers up to 512 NS values (NS = 0: it is read
-// again, for longer rows).
+// again, for longer rows).  Bound by memory latency at few rows (517 x 4096 with
+// 3 splits 17 us), by traffic at many (2048 x 4096: 39 -> 14 us, 3.5 TB/s).
 template <int NS>
 __global__ __launch_bounds__(512) void bprep_rows_kernel(PfRows a) {
     const int lane = threadIdx.x & 63, r = 8 * blockIdx.x + (threadIdx.x >> 6);
@@ -1161,6 +1162,11 @@ hipError_t launch_bprep_rows(const PfRows& a, hipStream_t st) {
 // starting value (one 16-byte LDS read), which leaves one multiply-add per
 // result and group.  The next group's codes and the one after's fragments are
 // in flight while a group computes.
+// Bound by issue: per 64 products a wave also issues about 165 vector
+// instructions (80 decode, 64 scale), and products and vector instructions of
+// the two waves of a SIMD overlap only in part (matrix cores busy half the time,
+// at about 1.8 GHz).  gate|up of 2048 tokens (8B) 622 -> 456 us, 1.05 PFLOP/s
+// (a large fp16 library product reaches 1.16 on this card).
 // RAG: K is not a multiple of 128 (operand entries past K are dropped).
 template <bool RAG>
 __global__ __launch_bounds__(256, 2) void gemm_pf_kernel(PfArgs a) {
@@ -2543,7 +2549,9 @@ hipError_t launch_attention(const AttnArgs& a, int head_dim, int queries_per_ite
 // of two LDS buffers per group while the step before computes; a wave reads the
 // step's K and V once for its QTW query tiles, and with one tile the LDS reads
 // (1024 cycles for the eight waves' steps) take longer than the products (768),
-// so QTW = 2 where the prompt has workgroups enough.
+// so QTW = 2 where the prompt has workgroups enough.  Bound by vector instructions
+// (about 140 per tile and step beside 25 products) and the steps' barriers: 2048
+// tokens of 32 x 128 heads 240 -> about 85 us a layer, 517 after 1536 170 -> 84.
 // Masked rows and rows past the block's last query enter as zeros with a -inf score.
 template <int D, int KVDT, int QTW>
 __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {

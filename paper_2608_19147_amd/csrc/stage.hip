@@ -84,6 +84,8 @@ void bp_plan(DevMat& m) {
 // K split of a prompt's residual product (o, down) over `tiles` workgroup tiles
 // of `ng` groups: the split that leaves the fullest CU the least work, a start
 // and an end counted as PF_SPLIT_COST groups; at most 8, at least 8 groups each.
+// (517 tokens, 8B down: 144 tiles on 256 CUs unsplit, 3-7 splits 76 us; 2048
+// tokens: 512 tiles, unsplit.)
 constexpr int PF_SPLIT_COST = 6;
 void pf_plan(int tiles, int ng, int n_cus, int& splits, int& kg) {
     int best = INT_MAX;

@@ -591,7 +591,9 @@ __device__ __forceinline__ void row_factors_finish(const GemvArgs& a, int K, boo
     }
 }
 
-// A bounds-checked buffer over `bytes` at p (loads past the end return zero).
+// A bounds-checked buffer over `bytes` at p: a load whose lane offset lies past
+// the end returns zero.  The uniform offset of buf_load16 is not checked: it only
+// takes places that are in range.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
 }
@@ -2587,8 +2589,10 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
         const __amdgpu_buffer_rsrc_t bk = buf_rsrc(kh + base, bytes), bv = buf_rsrc(vh + base, bytes);
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
-            rk[u] = buf_load16(bk, 16u * tg, 4096u * u);
-            rv[u] = buf_load16(bv, 16u * tg, 4096u * u);
+            // the piece's place is in the lane offset: the uniform offset takes no
+            // part in the bounds check that zeroes the rows at and past kend
+            rk[u] = buf_load16(bk, 16u * tg + 4096u * u, 0);
+            rv[u] = buf_load16(bv, 16u * tg + 4096u * u, 0);
         }
         word = a.mask ? a.mask[min(st, nsteps - 1)] : ~0u;
     };

@@ -643,7 +643,8 @@ __global__ __launch_bounds__(256 * PT, 2) void gemm_bp_kernel(GemvArgs a) {
     float (*red)[MP][65] = (float (*)[MP][65])(raw + (size_t)tl * 4 * MP * 65 * 4);
     float (*sres)[64] = sres_[tl], *sgam = sgam_[tl], *srs = srs_[tl];
     const int M = a.M, K = W.k;
-    const int g0 = (4 * s + w) * a.kg, g1 = min(W.ngroups, g0 + a.kg);
+    // groups of K itself: the matrix may be padded by more, the prepared rows are not
+    const int g0 = (4 * s + w) * a.kg, g1 = min((K + 127) / 128, g0 + a.kg);
     uint32_t magic = 0x64006400u;
     asm volatile("" : "+v"(magic));
     const __amdgpu_buffer_rsrc_t rw = buf_rsrc(W.w + (size_t)t * W.nchunk * 1024, (uint32_t)W.nchunk * 1024);

@@ -61,3 +61,18 @@ def test_row_result_does_not_depend_on_the_product_form():
             s.free()
     assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
     p.close()
+
+
+@pytest.mark.parametrize("n", [5, 40])
+def test_padded_matrix(n):
+    """The down matrix of this shape (249 chunks of 32 k) is stored with 64 groups
+    of 128 k where the prepared rows hold the 63 that K = 7968 takes."""
+    shape = synth.StageShape("padded", 8, n_layers=1, hidden=2048, n_q_heads=2, n_kv_heads=1, head_dim=128, ffn=7968)
+    p = Pair(shape, 440)
+    g, o = p.states(1, 70, 70 + n, 440)
+    x = synth.make_hidden(shape, n, 440)
+    pos = (70 + np.arange(n))[None]
+    out = run_gpu(p, [req(g, pos, full_mask(1, 70 + n))], x)
+    ref = oracle.forward(p.orc, o, host(x), pos, None, full_mask(1, 70 + n))
+    assert rel_err(out, ref) <= TOL_STAGE
+    p.close()

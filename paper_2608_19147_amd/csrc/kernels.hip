@@ -2553,7 +2553,7 @@ hipError_t launch_attention(const AttnArgs& a, int head_dim, int queries_per_ite
 // step's K and V once for its QTW query tiles, and with one tile the LDS reads
 // (1024 cycles for the eight waves' steps) take longer than the products (768),
 // so QTW = 2 where the prompt has workgroups enough.  Bound by vector instructions
-// (about 140 per tile and step beside 25 products) and the steps' barriers: 2048
+// (about 150 per tile and step beside 24 products) and the steps' barriers: 2048
 // tokens of 32 x 128 heads 240 -> about 85 us a layer, 517 after 1536 170 -> 84.
 // Masked rows and rows past the block's last query enter as zeros with a -inf score.
 template <int D, int KVDT, int QTW>
@@ -2621,10 +2621,7 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
     u32x4 qh[QTW][DB], qr[QTW][DB];
     int qtok[QTW];
     float base[QTW];                                         // what is subtracted from the scores (-inf: no key seen yet)
-    f32x4_t lacc[QTW];                                       // sums of the rounded probabilities, the same in every row
-    u32x4 ones;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) ones[e] = KVDT == DT_BF16 ? 0x3F803F80u : 0x3C003C00u;
+    float lsum[QTW];                                         // sums of this lane's probabilities (fp32, not rounded)
     f32x4_t nb[QTW];                                         // -base (0 before the first key), the score products' start
     f32x4_t o[QTW][MB];
 #pragma unroll
@@ -2634,7 +2631,8 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
         const int i = ok ? r / gs : a.n - 1, h = g * gs + (ok ? r % gs : 0);   // the last row stands in past the end
         qtok[u] = i;
         base[u] = -INFINITY;
-        nb[u] = lacc[u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        lsum[u] = 0.f;
+        nb[u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
         const float* qrow = a.qkv + (size_t)i * a.qkv_ld + (size_t)h * D;
         const float2* rp = a.rope + (size_t)a.pos[i] * HALF;
 #pragma unroll
@@ -2736,8 +2734,7 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
             // A step in which no query's largest score rises has no exchange between
             // lanes and no correction.  (Letting the base lag by up to 8 saved more,
             // but the largest key's probability was then rounded too: the error
-            // against 64 bits grew by 3%.)  The sum is taken of the rounded
-            // probabilities, one product with ones.
+            // against 64 bits grew by 3%.)
             if (__any(mx > (base[u] == -INFINITY ? -INFINITY : 0.f))) {
                 float x0f, x1f;
                 lane_pair_k(mx, 16, x0f, x1f);
@@ -2751,8 +2748,7 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
                 base[u] = first ? mx : base[u] + up;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) nb[u][j] -= up;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) lacc[u][j] *= corr;
+                lsum[u] *= corr;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) sv[e] -= up;
 #pragma unroll
@@ -2763,22 +2759,30 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
             float pv[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) pv[e] = __builtin_amdgcn_exp2f(sv[e]);
+            lsum[u] += ((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7]));
             u32x4 pb;
 #pragma unroll
             for (int w2 = 0; w2 < 4; ++w2) pb[w2] = kv_pack2<KVDT>(pv[2 * w2], pv[2 * w2 + 1]);
-            lacc[u] = mma_kv<KVDT>(ones, pb, lacc[u]);
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) o[u][mb] = mma_kv<KVDT>(vf[mb], pb, o[u][mb]);
         }
     }
 
     // ---- the two key groups' (base, sum, output) through LDS, then the o product's input
+#pragma unroll
+    for (int u = 0; u < QTW; ++u) {                          // a query's sum: the four lanes that hold its keys
+        float x0f, x1f;
+        lane_pair_k(lsum[u], 16, x0f, x1f);
+        lsum[u] = x0f + x1f;
+        lane_pair_k(lsum[u], 32, x0f, x1f);
+        lsum[u] = x0f + x1f;
+    }
     __syncthreads();                                         // no wave reads its step's rows any more
     f32x4_t* so = (f32x4_t*)&kv[0][0][0][0];                 // [4 QTW tiles][MB][64 lanes]
     if (kg == 1) {
 #pragma unroll
         for (int u = 0; u < QTW; ++u) {
-            sml[qw + 4 * u][lane] = float2{base[u], lacc[u][0]};
+            sml[qw + 4 * u][lane] = float2{base[u], lsum[u]};
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) so[((qw + 4 * u) * MB + mb) * 64 + lane] = o[u][mb];
         }
@@ -2791,7 +2795,7 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
         const float2 ml = sml[qw + 4 * u][lane];
         const float mn = fmaxf(base[u], ml.x);               // finite: every query sees its own row
         const float f0 = __builtin_amdgcn_exp2f(base[u] - mn), f1 = __builtin_amdgcn_exp2f(ml.x - mn);
-        const float inv = 1.0f / (lacc[u][0] * f0 + ml.y * f1);
+        const float inv = 1.0f / (lsum[u] * f0 + ml.y * f1);
         const int m = qtok[u], h = g * gs + r % gs;
         uint16_t* bp = a.bp + (size_t)(m >> 6) * 64 * a.kp;
         float* bc = a.bc + (size_t)(m >> 6) * 2 * a.kp;

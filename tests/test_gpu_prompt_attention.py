@@ -1,15 +1,18 @@
 """The prompt's attention (head_dim 128) at the edges of its 32-key steps: the
 rows of a state's buffer past the last key a block sees are never read into the
-result, whatever they hold.
+result, whatever they hold; and the softmax sum of the prompt is that of a
+forward (fp32 probabilities, not the rounded ones of the value product).
 
-Tolerance: TOL_STAGE, the stage tolerance every parity test uses."""
+Tolerance: TOL_STAGE, the stage tolerance every parity test uses, unless the
+test states its own."""
 import numpy as np
 import pytest
 import torch
 
 import oracle
+import oracle.stage_oracle as math
 import synth
-from gpu_cases import TOL_STAGE, Pair, host, rel_err
+from gpu_cases import TOL_STAGE, Pair, full_mask, host, rel_err, req, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -51,3 +54,40 @@ def test_rows_past_the_last_key_are_not_read(narrow, P0, n, holes):
     ref = oracle.forward(narrow.orc, o, host(x), pos[None], None, np.concatenate([past, np.ones(n, np.uint8)])[None])
     assert rel_err(out, ref) <= TOL_STAGE
     g.free()
+
+
+def test_softmax_sum_is_that_of_a_forward():
+    """Keys whose probability 0.5 (1 + 0.8 / 256) lies below the middle of two
+    bf16 values: the value product takes them as 0.5, the sum must not, in the
+    prompt as in a forward.  A sum of rounded probabilities would change the
+    attention output by 0.8 / 256 = 3.1e-3 of it; the two paths otherwise differ
+    by fp16 / fp32 roundings (hidden_out fp16: 2^-11 at most)."""
+    sh = synth.StageShape("narrow128f16", 9, n_layers=1, hidden=256, n_q_heads=2, n_kv_heads=1, head_dim=128, ffn=512,
+                          act_dtype=synth.F16)
+    layers = synth.make_weights(sh, 450)
+    for m in ("wk", "wv", "wd"):                             # own rows: score 0, value 0; no FFN output
+        layers[0].mats[m] = synth.zero_quant_like(layers[0].mats[m])
+    p = Pair(sh, 450, layers=layers)
+    P, n, D = 512, 2, 128
+    x = (synth.make_hidden(sh, n, 450).float() / 256).half()
+    pos = P + np.arange(n)
+    w = p.orc.weights(0)
+    h = math.rmsnorm(host(x), w["attn_norm"], sh.rms_eps)
+    q = math.apply_rope(math.gemv_rows(h, w["wq"]).reshape(n, 2, D), pos[:, None], sh.rope_theta).reshape(2 * n, D)
+    key = np.linalg.pinv(q) @ np.full(2 * n, np.log(0.5 * (1 + 0.8 / 256)) * np.sqrt(D))
+    k = torch.zeros((1, 1, 1, P, D))
+    k[0, 0, 0, :] = torch.from_numpy(key).float()
+    k[0, 0, 0, ::32] = 0                                     # the largest score, 0, in every step
+    v = torch.ones_like(k)
+    outs = []
+    for prompt in (True, False):
+        g = p.gpu.new_state(1, P + 8)
+        g.append(k.bfloat16(), v.bfloat16())
+        outs.append(host(p.gpu.prefill(g, pos, x.cuda())) if prompt
+                    else run_gpu(p, [req(g, pos[None], full_mask(1, P + n))], x))
+        g.free()
+    a, b = (o - host(x) for o in outs)
+    e = float(np.linalg.norm(a - b) / np.linalg.norm(b))
+    print(f"prompt against forward: {e:.2e}")
+    assert e <= 1e-3
+    p.close()

@@ -12,14 +12,13 @@ constexpr int MAX_ROWS = 64;         // activation rows per forward
 constexpr int GEMV_MAX_M = 8;        // rows one GEMV launch handles
 constexpr int GEMV_MAX_CPS = 64;     // chunks per workgroup: 4 waves x at most 16 chunks
 constexpr int ATTN_MAX_SPLITS = 64;  // KV splits per (slot, kv head)
-// Fewest keys per split of a request with `vectors` query vectors per kv head
-// (its tokens times the query heads of a kv head).  A workgroup with most of its
-// four tiles taken works longer per key, so its splits are shorter: 8B tree of
-// 15 nodes (60 vectors) at KV 2048 2.43 ms a step pair at 256, 2.27 at 128, 2.44
-// at 64.  Fewer vectors come in batches, whose requests fill the device: mixed
-// micro-batch of 8 3.37 ms at 256, 3.81 at 128; more are several workgroups per
-// split: 64 rows 4.69 ms at 256, 4.90 at 128.
-constexpr int attn_min_split(int vectors) { return vectors > 32 && vectors <= 64 ? 128 : 256; }
+// Fewest keys per split, the same for every request: a row's result must not
+// depend on how many tokens share its request (a verify's rows are those of a
+// shorter or longer one).  128 for requests of 33 to 64 query vectors per kv head
+// gave 8B trees of 15 nodes 7% (2.43 -> 2.27 ms a step pair at KV 2048), and split
+// a row's keys by its company.  128 for all: mixed micro-batch of 8 3.81 ms, at
+// 256 3.37; 64 rows 4.90 and 4.69.
+constexpr int ATTN_MIN_SPLIT = 256;
 constexpr int KGROUPS = 16;          // 16-lane key groups per attention workgroup
 
 enum Dt : int { DT_F32 = 0, DT_F16 = 1, DT_BF16 = 2 };

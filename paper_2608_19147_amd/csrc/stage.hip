@@ -1758,7 +1758,7 @@ int stage_forward(Stage* st, const StageRequest* reqs, int n_req, const void* hi
             if (const char* e = std::getenv("STAGE_ATTN_SPLITS")) splits = std::max(1, std::min(ATTN_MAX_SPLITS, atoi(e)));
             {                                            // the direct-load attention stages a whole split's table
                 const int Lr = d.P + n;
-                int sl = std::max(attn_min_split(gs * n), (Lr + splits - 1) / splits);
+                int sl = std::max(ATTN_MIN_SPLIT, (Lr + splits - 1) / splits);
                 sl = (sl + KGROUPS - 1) / KGROUPS * KGROUPS;
                 d.split_len = sl;
                 max_splits = std::max(max_splits, (Lr + sl - 1) / sl);

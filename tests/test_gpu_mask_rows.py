@@ -11,6 +11,8 @@ speculation needs a per-query mask).
   * a request with row masks beside one without leaves the latter bitwise
     unchanged; the vector-unit attention; a single decode row with a row
     mask (the single launch) equals its 2-D form bitwise;
+  * a row's result is bitwise the same however many tokens follow it in its
+    request (8B layer: 8 to 128 query vectors per kv head);
   * a query row that sees no key is refused."""
 import os
 
@@ -191,3 +193,18 @@ def test_row_with_no_visible_key_is_refused(tiny):
         run_gpu(tiny, [rq(g, np.array([[10, 11, 12]]), None, rows)], x)
     assert ei.value.code == -1 and g.length == 10
     g.free()
+
+
+def test_row_does_not_depend_on_the_tokens_behind_it():
+    """One 8B layer from KV 600 (several splits): the first two rows of requests of
+    2, 9, 16 and 32 tokens (8, 36, 64 and 128 query vectors per kv head)."""
+    p = Pair(synth.with_layers(synth.LLAMA8B_HALF, 1), 201, with_oracle=False)
+    x = synth.make_hidden(p.shape, 32, 201)
+    outs = []
+    for n in (2, 9, 16, 32):
+        g, _ = p.states(1, 600, 640, 201, with_oracle=False)
+        outs.append(run_gpu(p, [rq(g, (600 + np.arange(n))[None], full_mask(1, 600 + n))], x[:n])[:2])
+        g.free()
+    for o in outs[1:]:
+        assert np.array_equal(outs[0], o)
+    p.close()

@@ -2555,7 +2555,10 @@ hipError_t launch_attention(const AttnArgs& a, int head_dim, int queries_per_ite
 // so QTW = 2 where the prompt has workgroups enough.  Bound by vector instructions
 // (about 150 per tile and step beside 24 products) and the steps' barriers: 2048
 // tokens of 32 x 128 heads 240 -> about 85 us a layer, 517 after 1536 170 -> 84.
-// Masked rows and rows past the block's last query enter as zeros with a -inf score.
+// Masked rows and rows past the block's last query enter as zeros with a -inf
+// score, and so, for each wave, do the rows of tokens past its last: a non-finite
+// row reaches no token before its group of 16 (a wave's 16 QTW query vectors lie
+// in one such group: QTW is 1 where an odd number of heads shares a kv head).
 template <int D, int KVDT, int QTW>
 __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
     constexpr int HALF = D / 2, NCH = D / 8, DB = D / 32, MB = D / 16, RB = 2 * D;
@@ -2626,7 +2629,7 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
     f32x4_t o[QTW][MB];
 #pragma unroll
     for (int u = 0; u < QTW; ++u) {
-        const int r = r0 + 16 * (qw + 4 * u) + ql;
+        const int r = r0 + 16 * (QTW * qw + u) + ql;
         const bool ok = r < R;
         const int i = ok ? r / gs : a.n - 1, h = g * gs + (ok ? r % gs : 0);   // the last row stands in past the end
         qtok[u] = i;
@@ -2660,7 +2663,10 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) o[u][mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
-    const int tok0 = __builtin_amdgcn_readfirstlane(min(R - 1, r0 + 16 * qw) / gs);          // the wave's first token: steps up to it are causal for all
+    // the wave's first token: steps up to it are causal for all; and the keys up to
+    // its last: later ones never meet this wave
+    const int tok0 = __builtin_amdgcn_readfirstlane(min(R - 1, r0 + 16 * QTW * qw) / gs);
+    const int kw = __builtin_amdgcn_readfirstlane(a.P + (min(R, r0 + 16 * QTW * (qw + 1)) - 1) / gs + 1);
 
     uint32_t cword = word;
     put(0);
@@ -2672,7 +2678,8 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
         cword = word;
         put(buf ^ 1);
         ld(st + 4);
-        if (st >= nsteps) continue;
+        const int seen = kw - AK * st;                       // keys of the step that some query of the wave may see (uniform)
+        if (seen <= 0) continue;                             // (past the last step too)
         const uint8_t* kb = kv[kg][buf][0];
         const uint8_t* vb = kv[kg][buf][1];
         u32x4 kf0[DB], kf1[DB], vf[MB];
@@ -2710,6 +2717,16 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
                                                       (__attribute__((address_space(3))) s16x4*)ad));
             }
             vf[mb] = u32x4{p[0][0], p[0][1], p[1][0], p[1][1]};
+        }
+        if (seen < AK) {                                     // later tokens' values enter as zeros: 0 * inf would reach this wave
+            u32x4 see;
+#pragma unroll
+            for (int w2 = 0; w2 < 4; ++w2) {
+                const int key = 16 * (w2 >> 1) + 4 * lg + 2 * (w2 & 1);
+                see[w2] = key + 1 < seen ? ~0u : key < seen ? 0xFFFFu : 0u;
+            }
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) vf[mb] &= see;
         }
         const bool all = w0 == ~0u && AK * st + AK - 1 <= a.P + tok0;   // every key of the step is seen by every query (uniform)
         const int kbase = AK * st + 4 * lg;
@@ -2782,17 +2799,17 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
     if (kg == 1) {
 #pragma unroll
         for (int u = 0; u < QTW; ++u) {
-            sml[qw + 4 * u][lane] = float2{base[u], lsum[u]};
+            sml[QTW * qw + u][lane] = float2{base[u], lsum[u]};
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) so[((qw + 4 * u) * MB + mb) * 64 + lane] = o[u][mb];
+            for (int mb = 0; mb < MB; ++mb) so[((QTW * qw + u) * MB + mb) * 64 + lane] = o[u][mb];
         }
     }
     __syncthreads();
     if (kg == 1) return;
 #pragma unroll
     for (int u = 0; u < QTW; ++u) {
-        const int r = r0 + 16 * (qw + 4 * u) + ql;
-        const float2 ml = sml[qw + 4 * u][lane];
+        const int r = r0 + 16 * (QTW * qw + u) + ql;
+        const float2 ml = sml[QTW * qw + u][lane];
         const float mn = fmaxf(base[u], ml.x);               // finite: every query sees its own row
         const float f0 = __builtin_amdgcn_exp2f(base[u] - mn), f1 = __builtin_amdgcn_exp2f(ml.x - mn);
         const float inv = 1.0f / (lsum[u] * f0 + ml.y * f1);
@@ -2805,7 +2822,7 @@ __global__ __launch_bounds__(512, 2) void attn_pf_kernel(PfAttnArgs a) {
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 const int mb = 2 * mp + q, k = h * D + 16 * mb + 4 * lg;
-                const f32x4_t ob = so[((qw + 4 * u) * MB + mb) * 64 + lane];
+                const f32x4_t ob = so[((QTW * qw + u) * MB + mb) * 64 + lane];
                 uint16_t c[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
@@ -2831,7 +2848,7 @@ hipError_t launch_attention_pf(const PfAttnArgs& a, int head_dim, int n_cus, hip
     // one workgroup runs per CU; two query tiles per wave take about 5/3 of one
     // tile's time a step, so they pay where they save a round of workgroups
     const size_t w1 = (R + 63) / 64 * a.Hkv, w2 = (R + 127) / 128 * a.Hkv;
-    const bool two = 5 * ((w2 + n_cus - 1) / n_cus) <= 3 * ((w1 + n_cus - 1) / n_cus);
+    const bool two = a.Hq / a.Hkv % 2 == 0 && 5 * ((w2 + n_cus - 1) / n_cus) <= 3 * ((w1 + n_cus - 1) / n_cus);
     const dim3 grid((unsigned)((R + (two ? 127 : 63)) / (two ? 128 : 64) * a.Hkv)), block(512);
     const bool bf = a.kv_dt == DT_BF16;
 #define ATTN_PF(D_)                                                                               \

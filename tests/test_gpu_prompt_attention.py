@@ -1,7 +1,8 @@
 """The prompt's attention (head_dim 128) at the edges of its 32-key steps: the
 rows of a state's buffer past the last key a block sees are never read into the
 result, whatever they hold; and the softmax sum of the prompt is that of a
-forward (fp32 probabilities, not the rounded ones of the value product).
+forward (fp32 probabilities, not the rounded ones of the value product); and a
+non-finite prompt row reaches no token before its group of 16.
 
 Tolerance: TOL_STAGE, the stage tolerance every parity test uses, unless the
 test states its own."""
@@ -19,7 +20,13 @@ pytestmark = pytest.mark.gpu
 # one kv head of two query heads: a block of 64 query vectors is 32 tokens, so
 # every block of a prompt after P0 rows sees a multiple of 32 keys plus P0 (the
 # last one, P0 + n)
+# (GROUPED: 1024 query vectors per block of 64 tokens; prompts of more than 1,024
+# tokens, on 256 CUs, take two query tiles per wave)
 NARROW = synth.StageShape("narrow128", 7, n_layers=2, hidden=256, n_q_heads=2, n_kv_heads=1, head_dim=128, ffn=512)
+
+SINGLE = synth.StageShape("narrow128mha", 10, n_layers=2, hidden=256, n_q_heads=2, n_kv_heads=2, head_dim=128, ffn=512)
+THREE = synth.StageShape("narrow128three", 12, n_layers=2, hidden=256, n_q_heads=3, n_kv_heads=1, head_dim=128, ffn=512)
+GROUPED = synth.StageShape("narrow128gqa", 11, n_layers=2, hidden=256, n_q_heads=16, n_kv_heads=1, head_dim=128, ffn=2048)
 
 
 @pytest.fixture(scope="module")
@@ -90,4 +97,21 @@ def test_softmax_sum_is_that_of_a_forward():
     e = float(np.linalg.norm(a - b) / np.linalg.norm(b))
     print(f"prompt against forward: {e:.2e}")
     assert e <= 1e-3
+    p.close()
+
+
+@pytest.mark.parametrize("shape,P0,n,bad", [(SINGLE, 0, 100, 41), (SINGLE, 21, 100, 60), (NARROW, 5, 100, 62), (THREE, 0, 100, 37),
+                                            (GROUPED, 3, 70, 36), (GROUPED, 0, 1100, 805)])
+def test_non_finite_row_reaches_no_earlier_group(shape, P0, n, bad):
+    p = Pair(shape, 460, with_oracle=False)
+    x = synth.make_hidden(shape, n, 460)
+    outs = []
+    for poison in (False, True):
+        g, _ = p.states(1, P0, P0 + n, 460, with_oracle=False)
+        if poison:
+            x[bad] = float("inf")
+        outs.append(host(p.gpu.prefill(g, P0 + np.arange(n), x.cuda())))
+        g.free()
+    assert np.isnan(outs[1][bad:]).any(axis=1).all()
+    assert np.array_equal(outs[0][:bad // 16 * 16], outs[1][:bad // 16 * 16])
     p.close()

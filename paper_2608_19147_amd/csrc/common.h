@@ -129,7 +129,7 @@ struct PfRows {
 
 struct AttnArgs {
     const float* qkv; int qkv_ld;
-    float* out; int out_ld;
+    float* out; int out_ld;  // null: bp_out only
     MetaDev meta;
     const float2* rope;      // [max_positions][D/2] (cos, sin)
     int layer, Hq, Hkv, kv_dt;
@@ -140,6 +140,8 @@ struct AttnArgs {
     uint16_t* bp_out; float* bc_out; int kp;   // the attention output also in prepared form (o product input, 64-row blocks)
     int dma;                 // 1: cache rows by direct loads (attn_dma_kernel) where the launch allows it: every
                              // split at most 1024 keys, per-row masks of at most 8 KB per split
+    int no_append;           // the rows of this forward are already in the cache (a prompt's): do not write
+                             // them (attn_kernel and attn_mma_kernel)
     // test support (null unless armed): the rotated queries [M][Hq][D] and the
     // scores q.k / sqrt(D) of every visible key [M][Hq][dbg_keys]
     float* dbg_q; float* dbg_logits; int dbg_keys;

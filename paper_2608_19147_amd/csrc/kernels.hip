@@ -1567,7 +1567,7 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
             }
             consume(j, kf, vf);
         }
-        if (r0 == 0) {                          // append: owner of row j writes it
+        if (r0 == 0 && !a.no_append) {          // append: owner of row j writes it
             for (int j = max(j0, P) + kg; j < j1; j += KGROUPS) {
                 const int i = j - P;
                 const int m = rowbase + i;
@@ -1658,7 +1658,7 @@ __global__ __launch_bounds__(D) void attn_merge_kernel(AttnArgs a) {
     __syncthreads();
     float O = 0.f;
     for (int s2 = 0; s2 < nsplit; ++s2) O += pp[(size_t)s2 * (D + 2) + 2 + d] * wgt[s2];
-    a.out[(size_t)m * a.out_ld + (size_t)h * D + d] = O * inv_s;
+    if (a.out) a.out[(size_t)m * a.out_ld + (size_t)h * D + d] = O * inv_s;
     if (a.bp_out)                                            // the o product's input (64-row blocks)
         bp_put(a.bp_out + (size_t)(m >> 6) * 64 * a.kp, a.bc_out + (size_t)(m >> 6) * 2 * a.kp, a.kp, m & 63, h * D + d,
                O * inv_s, true);
@@ -1860,7 +1860,7 @@ __global__ __launch_bounds__(256, QTW == 1 ? 2 : 1) void attn_mma_kernel(AttnArg
         stab[tid + 256 * t2] = ptab[t2];
     }
     __syncthreads();
-    fetch(0, true);
+    fetch(0, !a.no_append);
     for (int qg = 0; qg < nqt; qg += 4 * QTW) {
         // ---- this wave's query tiles: rotated, scaled, split into rounded part and residual
         u32x4 qh[QTW][DB], qr[QTW][DB];
@@ -1946,14 +1946,14 @@ __global__ __launch_bounds__(256, QTW == 1 ? 2 : 1) void attn_mma_kernel(AttnArg
                 stab[x] = j < P ? tab[j] : (int16_t)b;
             }
             __syncthreads();
-            fetch(0, qg == 0);
+            fetch(0, qg == 0 && !a.no_append);
         }
         const int nsteps = (c1 - c0 + AK - 1) / AK;
         stash(0);
         __syncthreads();
         for (int st = 0; st < nsteps; ++st) {
             const int buf = st & 1;
-            if (st + 1 < nsteps) fetch((st + 1) * AK, qg == 0);   // next step's loads fly during this one
+            if (st + 1 < nsteps) fetch((st + 1) * AK, qg == 0 && !a.no_append);   // next step's loads fly during this one
             // the lane's 8 keys: step key 4 lg + e (e < 4) or 16 + 4 lg + e - 4; visible ones as bits
             const int kbase = c0 + st * AK + 4 * lg;
             uint32_t vbits = 0u;

@@ -43,6 +43,7 @@ int fail(int code, const std::string& msg) {
 
 constexpr int META_RING = 4;
 constexpr int PF_ROWS = 2048;            // prompt rows per prefill pass (all layers)
+static_assert(PF_ROWS * 2 <= MAX_ROWS * ATTN_MAX_SPLITS, "attention partials of a prefill pass");
 
 // Looks up the address of `scratch` on the current device `dev` once.
 int scratch_init(int dev) {
@@ -1406,7 +1407,19 @@ int stage_prefill(Stage* st, KVState* kv, int n, const int32_t* positions, const
     for (int jj = 0; past_mask && jj < P0 && !masked; ++jj) masked = !past_mask[jj];
     const size_t off_mask = align16(sizeof(int) * n);
     const size_t n_words = masked ? ((size_t)P0 + n + 31) / 32 : 0;
-    const size_t total = align16(off_mask + 4 * n_words);
+    // with STAGE_ATTN_VECTOR=1 or STAGE_ATTN_DMA=0 the prompt takes the forward's
+    // vector or register-staged attention, as a micro-batch of 16-row requests
+    // whose past includes the earlier ones' rows: a second form of attn_pf_kernel
+    const bool as_batch = st->attn_vector || !st->attn_dma;
+    constexpr int PF_REQ = 16;
+    const int nreq = as_batch ? (n + PF_REQ - 1) / PF_REQ : 0;
+    size_t mask_bytes = 0;
+    for (int q = 0; q < nreq; ++q) mask_bytes += (size_t)P0 + std::min(n, (q + 1) * PF_REQ);
+    const size_t off_req = align16(off_mask + 4 * n_words);
+    const size_t off_item = align16(off_req + sizeof(ReqDev) * nreq);
+    const size_t off_ritem = align16(off_item + sizeof(ItemDev) * nreq);
+    const size_t off_rmask = align16(off_ritem + (as_batch ? sizeof(int) * n : 0));
+    const size_t total = align16(off_rmask + mask_bytes);
     int rc = ensure_meta(st, total);
     if (rc) return rc;
     const int slot_i = st->ring_i;
@@ -1419,6 +1432,33 @@ int stage_prefill(Stage* st, KVState* kv, int n, const int32_t* positions, const
         std::memset(w, 0xFF, 4 * n_words);
         for (int jj = 0; jj < P0; ++jj)
             if (!past_mask[jj]) w[jj >> 5] &= ~(1u << (jj & 31));
+    }
+    constexpr int req_splits = 2;                      // per (request, kv head): the requests fill the device
+    size_t moff = 0;
+    for (int q = 0; q < nreq; ++q) {
+        const int r0 = q * PF_REQ, m = std::min(PF_REQ, n - r0);
+        ReqDev d{};
+        d.P = P0 + r0;
+        d.n = m;
+        d.S = 1;
+        d.row0 = r0 % PF_ROWS;                         // rows, items and row_item count from the start of the pass
+        d.cap = kv->cap;
+        d.mask_off = (int)moff;
+        d.mask_len = P0 + r0 + m;
+        d.rowmask_off = -1;
+        d.item0 = d.row0 / PF_REQ;
+        d.split_len = std::max(ATTN_MIN_SPLIT, (d.mask_len + req_splits - 1) / req_splits);
+        d.split_len = (d.split_len + KGROUPS - 1) / KGROUPS * KGROUPS;
+        d.kc = kv->kc;
+        d.vc = kv->vc;
+        d.table = kv->table[kv->cur];
+        ((ReqDev*)(hb + off_req))[q] = d;
+        ((ItemDev*)(hb + off_item))[q] = ItemDev{d.item0, 0, d};
+        for (int i = 0; i < m; ++i) ((int*)(hb + off_ritem))[r0 + i] = d.item0;
+        uint8_t* mk = hb + off_rmask + moff;
+        for (int jj = 0; jj < P0; ++jj) mk[jj] = !past_mask || past_mask[jj] ? 1 : 0;
+        std::memset(mk + P0, 1, (size_t)r0 + m);
+        moff += (size_t)d.mask_len;
     }
     uint8_t* db = st->meta_dev;
     HIP_TRY(hipMemcpyAsync(db, hb, total, hipMemcpyHostToDevice, s));
@@ -1504,25 +1544,55 @@ int stage_prefill(Stage* st, KVState* kv, int n, const int32_t* positions, const
                 HIP_TRY(launch_kv_rope_append(st->pf_qkv, nqkv, (const int*)db + p0, st->rope, pr, P0 + p0, Hq, Hkv,
                                               D, kv->kc + (size_t)l * lstride, kv->vc + (size_t)l * lstride, kv->cap,
                                               first ? kv->table[kv->cur] : nullptr, dt_code(c.kv_dtype), s));
-                PfAttnArgs a{};
-                a.qkv = st->pf_qkv;
-                a.qkv_ld = nqkv;
-                a.pos = (const int*)db + p0;
-                a.rope = st->rope;
-                a.kl = kv->kc + (size_t)l * lstride;
-                a.vl = kv->vc + (size_t)l * lstride;
-                a.cap = kv->cap;
-                a.P = P0 + p0;
-                a.n = pr;
-                a.Hq = Hq;
-                a.Hkv = Hkv;
-                a.kv_dt = dt_code(c.kv_dtype);
-                a.mask = masked ? (const uint32_t*)(db + off_mask) : nullptr;
-                a.qscale = (float)(1.4426950408889634 / std::sqrt((double)D));
-                a.bp = st->pf_bp[0];
-                a.bc = st->pf_bc[0];
-                a.kp = kin;
-                HIP_TRY(launch_attention_pf(a, D, st->n_cus, s));
+                if (as_batch) {
+                    const int q0 = p0 / PF_REQ, nq = (pr + PF_REQ - 1) / PF_REQ;
+                    AttnArgs a{};
+                    a.qkv = st->pf_qkv;
+                    a.qkv_ld = nqkv;
+                    a.meta.reqs = (const ReqDev*)(db + off_req) + q0;
+                    a.meta.items = (const ItemDev*)(db + off_item) + q0;
+                    a.meta.positions = (const int*)db + p0;
+                    a.meta.row_item = (const int*)(db + off_ritem) + p0;
+                    a.meta.masks = db + off_rmask;
+                    a.meta.n_items = nq;
+                    a.meta.M = pr;
+                    a.meta.n_req = nq;
+                    a.rope = st->rope;
+                    a.layer = l;
+                    a.Hq = Hq;
+                    a.Hkv = Hkv;
+                    a.kv_dt = dt_code(c.kv_dtype);
+                    a.qscale = (float)(1.4426950408889634 / std::sqrt((double)D));
+                    a.part = st->apart;                          // PF_ROWS x 2 splits: no more than MAX_ROWS x ATTN_MAX_SPLITS
+                    a.counters = st->acnt;
+                    a.nsplit_max = req_splits;
+                    a.vector_path = st->attn_vector;
+                    a.bp_out = st->pf_bp[0];
+                    a.bc_out = st->pf_bc[0];
+                    a.kp = kin;
+                    a.no_append = 1;
+                    HIP_TRY(launch_attention(a, D, (Hq / Hkv) * PF_REQ, s));
+                } else {
+                    PfAttnArgs a{};
+                    a.qkv = st->pf_qkv;
+                    a.qkv_ld = nqkv;
+                    a.pos = (const int*)db + p0;
+                    a.rope = st->rope;
+                    a.kl = kv->kc + (size_t)l * lstride;
+                    a.vl = kv->vc + (size_t)l * lstride;
+                    a.cap = kv->cap;
+                    a.P = P0 + p0;
+                    a.n = pr;
+                    a.Hq = Hq;
+                    a.Hkv = Hkv;
+                    a.kv_dt = dt_code(c.kv_dtype);
+                    a.mask = masked ? (const uint32_t*)(db + off_mask) : nullptr;
+                    a.qscale = (float)(1.4426950408889634 / std::sqrt((double)D));
+                    a.bp = st->pf_bp[0];
+                    a.bc = st->pf_bc[0];
+                    a.kp = kin;
+                    HIP_TRY(launch_attention_pf(a, D, st->n_cus, s));
+                }
             }
             HIP_TRY(prof_mark(st, STAGE_KERNEL_ATTN, false, s));
             // x = residual + o W_o^T

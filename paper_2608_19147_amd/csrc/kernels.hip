@@ -615,8 +615,9 @@ __device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t o
 // with -1.  That leaves one multiply-add per result and group.
 // Z = 2: 33..64 rows, as two workgroups of 32 rows per tile that run one after
 // the other on one XCD (the second finds the codes in its L2).
-// PT = 2: eight waves take two tiles; the two waves of a K range fetch half of
-// its prepared rows each and share them through LDS.  With every wave fetching
+// PT = 2 (17 or more rows of a product that is neither split over K nor adds to
+// a residual): eight waves take two tiles; the two waves of a K range fetch half
+// of its prepared rows each and share them through LDS.  With every wave fetching
 // its own, the caches delivered about 9.5 TB/s and bound the product: the LM
 // head (20 rows, 8 KB of rows per 4 KB of codes) streamed its codes at 3.1 TB/s,
 // at 16 rows (4 KB) 4.3.
@@ -629,7 +630,8 @@ __global__ __launch_bounds__(256 * PT, 2) void gemm_bp_kernel(GemvArgs a) {
     constexpr int SBB = PT == 2 ? 2 * 4 * 4 * NCB * 1024 : 0, REDB = PT * 4 * MP * 65 * 4;
     __shared__ __attribute__((aligned(16))) uint8_t raw[SBB > REDB ? SBB : REDB];
     __shared__ float fs[64];
-    __shared__ float sres_[PT][NCB >= 2 ? MP : 1][64], sgam_[PT][64], srs_[PT][NCB >= 2 ? MP : 1];   // residual-epilogue inputs read at the start
+    constexpr bool PRE = NCB >= 2 && PT == 1;
+    __shared__ float sres[PRE ? MP : 1][64], sgam[PRE ? 64 : 1], srs[PRE ? MP : 1];   // residual-epilogue inputs read at the start
     __shared__ int last_s;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = wave & 3;   // uniform: scalar loop control
     const int tl = wave >> 2, tid = threadIdx.x & 255, lane = tid & 63;   // tile of the workgroup, thread of the tile
@@ -641,7 +643,6 @@ __global__ __launch_bounds__(256 * PT, 2) void gemm_bp_kernel(GemvArgs a) {
     const bool has = PT * wg + tl < W.ntiles;
     const int t = has ? PT * wg + tl : W.ntiles - 1;            // an odd matrix's missing tile repeats the last; its results are dropped
     float (*red)[MP][65] = (float (*)[MP][65])(raw + (size_t)tl * 4 * MP * 65 * 4);
-    float (*sres)[64] = sres_[tl], *sgam = sgam_[tl], *srs = srs_[tl];
     const int M = a.M, K = W.k;
     // groups of K itself: the matrix may be padded by more, the prepared rows are not
     const int g0 = (4 * s + w) * a.kg, g1 = min((K + 127) / 128, g0 + a.kg);
@@ -764,7 +765,6 @@ __global__ __launch_bounds__(256 * PT, 2) void gemm_bp_kernel(GemvArgs a) {
     // of the tile, off the last split's tail; the residual is rewritten only by
     // the tile's last split to arrive, after all have started.  (With 16 rows the
     // added start latency outweighs the shorter tail: measured.)
-    constexpr bool PRE = NCB >= 2;
     const bool resid_epi = PRE && a.epi == EPI_RESID;
     float pres[NV], prs = 0.f;
     uint16_t pgam_bits = 0;
@@ -871,15 +871,15 @@ __global__ __launch_bounds__(256 * PT, 2) void gemm_bp_kernel(GemvArgs a) {
     }
 
     // ---- split-K: the last workgroup of the tile sums every split in split order
-    if (a.ksplit > 1) {
+    if (PT == 1 && a.ksplit > 1) {
         const int ldp = W.ntiles * 64;
 #pragma unroll
         for (int q = 0; q < NV; ++q) {
             const int idx = tid + 256 * q;
-            if (has && m0 + (idx >> 6) < M)
+            if (m0 + (idx >> 6) < M)
                 store_coherent(&a.partial[((size_t)s * M + m0 + (idx >> 6)) * ldp + t * 64 + (idx & 63)], vals[q]);
         }
-        if (!last_arrival(&a.counters[Z == 1 ? wg : 2 * wg + (m0 >> 5)], (unsigned)a.ksplit, &last_s)) return;
+        if (!last_arrival(&a.counters[Z == 1 ? t : 2 * t + (m0 >> 5)], (unsigned)a.ksplit, &last_s)) return;
         const size_t stride = (size_t)M * ldp;
 #pragma unroll
         for (int q = 0; q < NV; ++q) vals[q] = 0.f;
@@ -911,7 +911,7 @@ __global__ __launch_bounds__(256 * PT, 2) void gemm_bp_kernel(GemvArgs a) {
                 if (n < W.n) a.out[(size_t)m * a.out_ld + n] = vals[q] * fs[m];
             }
         }
-    } else if (a.epi == EPI_RESID) {
+    } else if (PT == 1 && a.epi == EPI_RESID) {
         // the residual rows, the next norm's weights and the rows' rs (read at the
         // start with 17 or more rows), every load issued before any is used
         float xres[NV], egam[NV], ers[NV];
@@ -934,7 +934,7 @@ __global__ __launch_bounds__(256 * PT, 2) void gemm_bp_kernel(GemvArgs a) {
             const int idx = tid + 256 * q;
             const int m = m0 + (idx >> 6), r = idx & 63;              // one row per wave: whole waves take part
             const int n = t * 64 + r;
-            const bool ok = m < Mt && n < W.n;
+            const bool ok = m < M && n < W.n;
             float xn = 0.f;
             if (ok) {
                 float xr;
@@ -946,8 +946,8 @@ __global__ __launch_bounds__(256 * PT, 2) void gemm_bp_kernel(GemvArgs a) {
             }
             // the row's sum of squares over the tile: row m is this wave's 64 lanes
             const float ss = wave_sum_all(xn * xn);
-            if (a.ssq_out && m < Mt && r == 0) a.ssq_out[(size_t)m * W.ntiles + t] = ss;
-            if (a.bp_out && m < Mt) {                                    // the next product's input
+            if (a.ssq_out && m < M && r == 0) a.ssq_out[(size_t)m * W.ntiles + t] = ss;
+            if (a.bp_out && m < M) {                                    // the next product's input
                 float c, gm;
                 if constexpr (PRE) {
                     c = srs[m - m0];
@@ -1003,7 +1003,9 @@ __global__ __launch_bounds__(256 * PT, 2) void gemm_bp_kernel(GemvArgs a) {
 
 hipError_t launch_gemm_bp(const GemvArgs& a, hipStream_t st) {
     if (a.M < 1 || a.M > 64 || a.W.gchunks != 4 || a.kg < 1 || a.kp % 128) return hipErrorInvalidValue;
-    if (a.pt != 1 && a.pt != 2) return hipErrorInvalidValue;
+    // two tiles per workgroup: more than 16 rows, both tiles' groups in the pair's
+    // order, whole sums, no residual
+    if (a.pt != 1 && (a.pt != 2 || a.M <= 16 || !a.pair_rot || a.ksplit != 1 || a.epi == EPI_RESID)) return hipErrorInvalidValue;
     const int wgs = (a.W.ntiles + a.pt - 1) / a.pt;
     const dim3 grid(wgs, a.ksplit), zgrid((wgs + 7) / 8 * 16, a.ksplit), block(256 * a.pt);
     if (a.pt == 1) {
@@ -1011,8 +1013,7 @@ hipError_t launch_gemm_bp(const GemvArgs& a, hipStream_t st) {
         else if (a.M <= 32) gemm_bp_kernel<2, 1, 1><<<grid, block, 0, st>>>(a);
         else gemm_bp_kernel<2, 2, 1><<<zgrid, block, 0, st>>>(a);
     } else {
-        if (a.M <= 16) gemm_bp_kernel<1, 1, 2><<<grid, block, 0, st>>>(a);
-        else if (a.M <= 32) gemm_bp_kernel<2, 1, 2><<<grid, block, 0, st>>>(a);
+        if (a.M <= 32) gemm_bp_kernel<2, 1, 2><<<grid, block, 0, st>>>(a);
         else gemm_bp_kernel<2, 2, 2><<<zgrid, block, 0, st>>>(a);
     }
     return hipGetLastError();

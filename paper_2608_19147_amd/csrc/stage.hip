@@ -105,16 +105,16 @@ void pf_plan(int tiles, int ng, int n_cus, int& splits, int& kg) {
 
 // Whether a prepared-operand product may take two weight tiles per workgroup,
 // which share the prepared rows, and whether M rows do: more than 16 (the rows
-// then outweigh the codes), with pairs enough to give most CUs a workgroup and 4
-// to 8 groups per wave (fewer do not repay the barriers; a pair's common rotation
+// then outweigh the codes), for a product that is not split over K and adds to no
+// residual, with pairs enough to give most CUs a workgroup and 4 to 8 groups per wave (fewer do not repay the barriers; a pair's common rotation
 // costs the long ranges of 70B gate|up 3% at one row).  gate|up of the 8B stage
 // (224 pairs of 8 groups): 20 rows 23.4 -> 20.1 us, 64 rows 46 -> 41.
-bool bp_pairable(const DevMat& m, int n_cus) {
-    const long pairs = (long)(m.pm.ntiles + 1) / 2 * m.bp_split;
-    return m.bp_kg >= 4 && m.bp_kg <= 8 && 4 * pairs >= 3L * n_cus;
+bool bp_pairable(const DevMat& m, int epi, int n_cus) {
+    const long pairs = (long)(m.pm.ntiles + 1) / 2;
+    return m.bp_split == 1 && epi != EPI_RESID && m.bp_kg >= 4 && m.bp_kg <= 8 && 4 * pairs >= 3L * n_cus;
 }
 void bp_form(GemvArgs& a, const DevMat& m, int M, int n_cus) {
-    a.pair_rot = bp_pairable(m, n_cus);
+    a.pair_rot = bp_pairable(m, a.epi, n_cus);
     a.pt = a.pair_rot && M > 16 ? 2 : 1;
 }
 
@@ -1331,7 +1331,6 @@ int stage_head_top1(Stage* st, const void* hidden, int M, int32_t* token_out, fl
     a.M = M;
     a.kp = st->kp;
     a.kg = st->head.bp_kg;
-    bp_form(a, st->head, M, st->n_cus);
     a.ksplit = 1;
     a.partial = st->gpart;
     a.counters = st->gcnt;
@@ -1340,6 +1339,7 @@ int stage_head_top1(Stage* st, const void* hidden, int M, int32_t* token_out, fl
     a.cb_in = st->cbf[0];
     a.norm = 2;
     a.epi = EPI_TOP1;
+    bp_form(a, st->head, M, st->n_cus);
     a.out = logits_out;
     a.out_ld = st->vocab;
     a.top1_part = st->top1_part;

@@ -8,8 +8,10 @@ its probability on the device).
   * the token equals the oracle's wherever the oracle's top-2 gap exceeds
     the logits tolerance, else the GPU's token is within it of the maximum;
   * p_max within 1e-3 absolute and 1e-2 relative of the oracle's;
-  * tiny head with a ragged last tile at 1, 5 and 64 rows, the Llama-3 sized
-    head (128256 x 4096) at 1 and 20 rows, and a stage forward chained into
+  * tiny head with a ragged last tile at 1, 5 and 64 rows, a head of an odd
+    number of tiles at 20 and 40 rows (two tiles per workgroup, the last pair's
+    second one missing), the Llama-3 sized head (128256 x 4096) at 1 and 20
+    rows, and a stage forward chained into
     the head against the oracle's forward + head."""
 import numpy as np
 import pytest
@@ -66,6 +68,20 @@ def test_head_tiny(tiny_head, M):
     p, fn, lm = tiny_head
     x = synth.make_hidden(p.shape, M, 171, M)
     _check(p.gpu, p.shape, fn, lm, x, f"tiny vocab 1000 M={M}")
+
+
+@pytest.mark.parametrize("M", [20, 40])
+def test_head_odd_tiles(M):
+    """383 tiles, the last of 24 rows: enough pairs (192 of 4 groups of 128 k per
+    wave) for three quarters of the CUs, so 17 or more rows take two tiles per
+    workgroup."""
+    shape = synth.StageShape("oddhead", 15, n_layers=1, hidden=2048, n_q_heads=2, n_kv_heads=1, head_dim=128, ffn=512)
+    assert 4 * 192 >= 3 * torch.cuda.get_device_properties(0).multi_processor_count
+    p = Pair(shape, 175, with_oracle=False)
+    fn, lm = synth.make_head(shape, 382 * 64 + 24, 175)
+    p.gpu.attach_head(fn, lm)
+    _check(p.gpu, shape, fn, lm, synth.make_hidden(shape, M, 176), f"383 tiles M={M}")
+    p.close()
 
 
 def test_head_sharp_rows(tiny_head):

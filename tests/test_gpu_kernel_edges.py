@@ -1,9 +1,12 @@
 """Edges of the prompt and product kernels against the oracle and each other:
-prompt lengths around the 64-token block, the 8-block band and the split of K
-(tiny stage, FFN 688: a ragged last group of k), past rows with masked holes at
-lengths around the attention's 32-key step and 64-query block; a row's result in
-a forward must be bitwise the same whichever product form its batch selects (16
-rows or fewer, 17-32, 33-64).
+prompt lengths around the 64-token block and the 8-block band (tiny stage, FFN
+688: a ragged last group of k; its products are too short to be split over K),
+past rows with masked holes at lengths around the attention's 32-key step and
+64-query block; residual products split over K with two query tiles per wave, two
+passes, and hidden sizes above 4,096 and 8,192 (narrow stages of two layers, so
+that a split product's sums enter the next layer and the output); a row's result
+in a forward must be bitwise the same whichever product form its batch selects
+(16 rows or fewer, 17-32, 33-64).
 
 Tolerance: TOL_STAGE, the stage tolerance every parity test uses (fp16 product
 inputs and 16-bit cache rows; 2.8e-3 measured on these paths)."""
@@ -45,6 +48,59 @@ def test_prompt_edges(tiny, P0, n, holes):
         assert rel_err(host(k), o.K[l][0][:, P0:P0 + n]) <= TOL_STAGE
         assert rel_err(host(v), o.V[l][0][:, P0:P0 + n]) <= TOL_STAGE
     g.free()
+
+
+def _splits(tiles, groups, cus):
+    """The K splits that a prompt's residual product of so many workgroup tiles and groups of 128 k takes."""
+    best = (1 << 30, 1)
+    for S in range(1, min(8, groups // 8) + 1):
+        per = -(-groups // S)
+        used = -(-groups // per)
+        best = min(best, (-(-tiles * used // cus) * (per + 6), used))     # the first of equal costs
+    return best[1]
+
+
+def _query_tiles(n, heads, kv_heads, cus):
+    """Query tiles per wave of a prompt's attention."""
+    rounds = [-(-(-(-n * heads // kv_heads // v) * kv_heads) // cus) for v in (64, 128)]
+    return 2 if heads // kv_heads % 2 == 0 and 5 * rounds[1] <= 3 * rounds[0] else 1
+
+
+# head_dim 128; (shape, P0, n, holes, query tiles per wave, o and down split over K)
+WIDE = [
+    (dict(hidden=256, n_q_heads=16, n_kv_heads=1, ffn=2048), 37, 1100, 0.2, 2, (True, True)),
+    (dict(hidden=256, n_q_heads=2, n_kv_heads=1, ffn=512), 19, 2100, 0.2, 1, (False, False)),     # passes of 2,048 and 52 rows
+    (dict(hidden=4104, n_q_heads=2, n_kv_heads=1, ffn=2048), 0, 70, 0, 1, (False, True)),
+    (dict(hidden=8200, n_q_heads=2, n_kv_heads=1, ffn=2048), 5, 70, 0, 1, (False, True)),
+]
+
+
+@pytest.mark.parametrize("dims,P0,n,holes,tiles,split", WIDE, ids=["two-tiles-split", "two-passes", "hidden4104", "hidden8200"])
+def test_prompt_forms(dims, P0, n, holes, tiles, split):
+    shape = synth.StageShape("wide", 14, n_layers=2, head_dim=128, **dims)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    m = min(n, 2048)                                        # rows of the first pass
+    assert _query_tiles(m, shape.n_q_heads, shape.n_kv_heads, cus) == tiles
+    blocks = -(-(-(-shape.hidden // 64)) // 4) * -(-m // 64)
+    for k, want in zip((shape.n_q_heads * shape.head_dim, shape.ffn), split):
+        assert (_splits(blocks, -(-k // 128), cus) > 1) == want
+    p = Pair(shape, 470)
+    g, o = p.states(1, P0, P0 + n + 8, 470)
+    past = np.ones(P0, np.uint8)
+    if holes:
+        past = synth.hole_mask(P0, holes, 470, 0)
+        past[0] = 1
+    x = synth.make_hidden(shape, n, 470, 1)
+    pos = int(past.sum()) + np.arange(n)
+    out = host(p.gpu.prefill(g, pos, x.cuda(), past if holes else None))
+    ref = oracle.forward(p.orc, o, host(x), pos[None], None, np.concatenate([past, np.ones(n, np.uint8)])[None])
+    print(f"{dims}: {rel_err(out, ref):.2e}")
+    assert rel_err(out, ref) <= TOL_STAGE
+    for l in range(shape.n_layers):
+        k, v = g.read(l, 0, P0, n)
+        assert rel_err(host(k), o.K[l][0][:, P0:P0 + n]) <= TOL_STAGE
+        assert rel_err(host(v), o.V[l][0][:, P0:P0 + n]) <= TOL_STAGE
+    p.close()
 
 
 def test_row_result_does_not_depend_on_the_product_form():

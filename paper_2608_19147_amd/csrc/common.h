@@ -129,7 +129,7 @@ struct PfRows {
 
 struct AttnArgs {
     const float* qkv; int qkv_ld;
-    float* out; int out_ld;  // null: bp_out only
+    float* out; int out_ld;
     MetaDev meta;
     const float2* rope;      // [max_positions][D/2] (cos, sin)
     int layer, Hq, Hkv, kv_dt;

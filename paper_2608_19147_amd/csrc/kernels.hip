@@ -1659,7 +1659,7 @@ __global__ __launch_bounds__(D) void attn_merge_kernel(AttnArgs a) {
     __syncthreads();
     float O = 0.f;
     for (int s2 = 0; s2 < nsplit; ++s2) O += pp[(size_t)s2 * (D + 2) + 2 + d] * wgt[s2];
-    if (a.out) a.out[(size_t)m * a.out_ld + (size_t)h * D + d] = O * inv_s;
+    a.out[(size_t)m * a.out_ld + (size_t)h * D + d] = O * inv_s;
     if (a.bp_out)                                            // the o product's input (64-row blocks)
         bp_put(a.bp_out + (size_t)(m >> 6) * 64 * a.kp, a.bc_out + (size_t)(m >> 6) * 2 * a.kp, a.kp, m & 63, h * D + d,
                O * inv_s, true);

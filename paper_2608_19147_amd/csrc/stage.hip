@@ -1549,6 +1549,8 @@ int stage_prefill(Stage* st, KVState* kv, int n, const int32_t* positions, const
                     AttnArgs a{};
                     a.qkv = st->pf_qkv;
                     a.qkv_ld = nqkv;
+                    a.out = st->pf_qkv;                          // scratch: the merge writes it, after the last read of q|k|v
+                    a.out_ld = nqkv;
                     a.meta.reqs = (const ReqDev*)(db + off_req) + q0;
                     a.meta.items = (const ItemDev*)(db + off_item) + q0;
                     a.meta.positions = (const int*)db + p0;

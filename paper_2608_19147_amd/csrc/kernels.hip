@@ -626,9 +626,13 @@ __global__ __launch_bounds__(256 * PT, 2) void gemm_bp_kernel(GemvArgs a) {
     constexpr int MP = 16 * NCB;
     constexpr int NV = MP * 64 / 256;
     // the shared rows [buffer][K range][fragment][lane] (PT = 2) and, after the
-    // products, the waves' sums [tile][wave][row][65]
-    constexpr int SBB = PT == 2 ? 2 * 4 * 4 * NCB * 1024 : 0, REDB = PT * 4 * MP * 65 * 4;
-    __shared__ __attribute__((aligned(16))) uint8_t raw[SBB > REDB ? SBB : REDB];
+    // products, the waves' sums [tile][wave][row][65].  PT = 2 takes more than half
+    // of a CU's 160 KB, though its registers already admit one workgroup per CU: LM
+    // head of 20 rows 87.5 us at 81 KB, 88.6 at the 65 KB it needs; 64 rows 4.30 and
+    // 4.31 ms.
+    constexpr int REDB = PT * 4 * MP * 65 * 4, RAWB = PT == 2 ? 81 * 1024 : REDB;
+    static_assert(RAWB >= REDB && (PT == 1 || RAWB >= 2 * 4 * 4 * NCB * 1024), "LDS of the rows and the sums");
+    __shared__ __attribute__((aligned(16))) uint8_t raw[RAWB];
     __shared__ float fs[64];
     constexpr bool PRE = NCB >= 2 && PT == 1;
     __shared__ float sres[PRE ? MP : 1][64], sgam[PRE ? 64 : 1], srs[PRE ? MP : 1];   // residual-epilogue inputs read at the start

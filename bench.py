@@ -35,8 +35,8 @@ same fields, no CPU baseline):
                 each timed call) and kv_capture of the kept rows to a device blob;
   prefill8b     prompt prefill on the 8B half stage: 2048 prompt tokens from an empty
                 cache (and 512 after 1536 cached rows), stage_prefill (passes of up
-                to 2048 rows through every layer: matrix-core products over the whole
-                pass, the causal attention of its 64-row chunks in one launch);
+                to 2048 rows through every layer: the matrix-core products and the
+                causal attention over the whole pass);
   tree8b        tree-shaped speculative verify on the 8B half stage: one slot at KV
                 2048, a 15-node binary draft tree (depth 3) in one forward with a
                 per-query-row mask (each node sees the cache and its ancestors);
@@ -328,7 +328,7 @@ def other_workload(args) -> int:
                     "launches_timed": launches}
             lin_flop = 2.0 * n * shape.weight_bytes() * 2 / 1.03   # ~2 int4 weights per byte (scales ~3% of bytes)
             cfg = {"workload": f"llama3.1-8b half stage prefill, {n} prompt tokens after {P0} cached rows", **base_cfg,
-                   "prompt_tokens": n, "kv_len_before": P0, "pass_rows": 2048, "attention_chunk_rows": 64}
+                   "prompt_tokens": n, "kv_len_before": P0, "pass_rows": 2048}
             lines.append(_line(f"prefill tokens/s (8B half-stage, {n} tokens after {P0})", n * 1e3 / ms, "tokens/s", args,
                                steps, ms, cfg, wbytes + (P0 + n) * kvb, roof,
                                linear_tflops=round(lin_flop / (ms * 1e-3) / 1e12, 1)))

@@ -303,9 +303,9 @@ int stage_forward(Stage* stage, const StageRequest* reqs, int n_req,
  * NULL (0 hides that past row from every prompt row).  Prompt row i sees the
  * past rows the mask keeps and prompt rows 0..i.  The result equals
  * stage_forward of the same rows with that mask, up to rounding: the prompt
- * goes through the layers in passes of at most 2048 rows (the products take a
- * whole pass at once, the attention its 64-row chunks in one launch, every
- * RMSNorm input is normalized in full).  Afterwards P += n.  Allocates a
+ * goes through the layers in passes of at most 2048 rows (the products and the
+ * attention take a whole pass in one launch each, every RMSNorm input is
+ * normalized in full).  Afterwards P += n.  Allocates a
  * workspace for min(n, 2048) rows on first use (kept, grown when a longer
  * prompt comes).
  * Errors: INVALID (NULL, overlap), SHAPE (state with more than one slot),

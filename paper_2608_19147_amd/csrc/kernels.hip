@@ -2146,10 +2146,11 @@ __device__ __forceinline__ void attn_vm() { asm volatile("s_waitcnt vmcnt(%0)" :
 __device__ __forceinline__ void attn_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // A workgroup takes 64 query vectors of one (item, kv head) and one split of its
-// keys, a tile of 16 per wave; items with more are spread over blockIdx.z, whose
-// workgroups read the same rows on the same XCD (several tiles per wave spilled
-// registers and left most CUs without work: 64 rows at KV 2048 were 72
-// workgroups, 60 us).
+// keys, a tile of 16 per wave; items with more are spread over blockIdx.z.  The
+// workgroups of one split's query blocks are items x kv heads x nsplit_max apart,
+// so they read the same rows on the same XCD where that is a multiple of 8 (8 kv
+// heads: always).  (Several tiles per wave spilled registers and left most CUs
+// without work: 64 rows at KV 2048 were 72 workgroups, 60 us.)
 template <int D, int KVDT, bool REC = false>
 __global__ __launch_bounds__(256, 2) void attn_dma_kernel(AttnArgs a) {
     constexpr int HALF = D / 2;

@@ -1,12 +1,12 @@
 """The attention whose cache rows arrive by direct-to-LDS loads (the default
-for items of at most 64 query vectors per kv head) against the register-staged
-form (STAGE_ATTN_DMA=0): same splits, steps and arithmetic, so the outputs and
+for splits of at most 1,024 keys) against the register-staged form
+(STAGE_ATTN_DMA=0): same splits, steps and arithmetic, so the outputs and
 the appended cache rows must be bitwise equal.  Cases: speculative verify on
 4 slots x 5 tokens from KV 2048 with 10% masked holes, a masked last draft and
 a beam permutation, then a decode step (two 8B layers); a micro-batch of
 decode and verify requests of several lengths; a 15-node draft tree with one
-key mask per query row; 24 and 64 rows of one slot (two and four query tiles
-per wave); a 70B-shaped layer verifying 5 tokens (40 query vectors per kv
+key mask per query row; 24 and 64 rows of one slot (two and four workgroups
+per split); a 70B-shaped layer verifying 5 tokens (40 query vectors per kv
 head: three tiles); and the tiny shape (head_dim 64).  The oracle checks of the default path run in the other GPU
 tests."""
 import os
@@ -144,9 +144,8 @@ def test_8b_tree_row_masks():
 
 @pytest.mark.parametrize("n", [24, 64])
 def test_8b_many_query_rows(n):
-    """24 rows (96 query vectors per kv head: two tiles per wave) and 64 rows
-    (256: four tiles per wave, the prefill chunk's shape), one slot from KV 700
-    with holes."""
+    """24 rows (96 query vectors per kv head: two workgroups per split, the second
+    half full) and 64 rows (256: four), one slot from KV 700 with holes."""
     shape = synth.with_layers(synth.LLAMA8B_HALF, 1)
     P = 700
     mask = np.ones((1, P + n), np.uint8)

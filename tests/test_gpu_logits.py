@@ -141,7 +141,7 @@ def test_8b_layer_logits_verify_kv2048():
 def test_8b_layer_logits_64_tokens_kv2048():
     """One 8B layer: one slot verifying 64 tokens (the row limit) from KV 2048
     with 10% holes and the last 14 drafts masked: 256 query vectors per kv
-    head, so two query tiles per wave and two passes over each split's keys."""
+    head, so four workgroups per split of the keys."""
     shape = synth.with_layers(synth.LLAMA8B_HALF, 1)
     p = _per_layer_pair(shape, 74)
     P, n = 2048, 64

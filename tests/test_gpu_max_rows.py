@@ -1,7 +1,6 @@
 """The row limit of one forward (STAGE_MAX_ROWS = 64) against the fp64 oracle,
-and the attention forms that only long verifies reach: more than 64 query
-vectors of one (slot, kv head) take two query tiles per wave, and more than
-128 take several passes over the split's keys.  One row beyond the limit is
+and the attention of long verifies: more than 64 query vectors of one (slot,
+kv head) take several workgroups per split of its keys.  One row beyond the limit is
 rejected and leaves the state unchanged."""
 import numpy as np
 import pytest
@@ -35,7 +34,7 @@ def _long_verify(p, P, n, seed, masked_from):
 
 
 def test_tiny_64_tokens_one_slot():
-    """128 query vectors per kv head: two query tiles per wave."""
+    """128 query vectors per kv head: two workgroups per split."""
     p = Pair(synth.with_layers(synth.TINY, 2), 91)
     _long_verify(p, 40, MAX_ROWS, 91, masked_from=44)
 

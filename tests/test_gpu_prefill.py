@@ -3,11 +3,12 @@ prompt goes through the stage in one pass that fills the cache; "NPU Stages:
 Static, Stateless Shards": long prompts in fixed-size chunks).
 
 The oracle runs the whole prompt as one forward (causal over the prompt rows,
-the past rows its mask keeps); stage_prefill runs it in chunks of 64 rows,
-layer-major.  Checked: hidden_out, every cache row the prefill appends (every
-layer), a decode after the prefill, chunk boundaries (64, 65 rows), a prompt
-after existing rows with masked holes, agreement with the same prompt fed
-through stage_forward chunk by chunk, an 8B-shaped layer, and the errors."""
+the past rows its mask keeps); stage_prefill takes it through the layers in
+passes of at most 2,048 rows, the products in blocks of 64.  Checked: hidden_out,
+every cache row the prefill appends (every layer), a decode after the prefill,
+block boundaries (64, 65 rows), a prompt after existing rows with masked holes,
+agreement with the same prompt fed through stage_forward 64 rows at a time, an
+8B-shaped layer, and the errors."""
 import numpy as np
 import pytest
 import torch

@@ -4,7 +4,8 @@ prompt lengths around the 64-token block and the 8-block band (tiny stage, FFN
 past rows with masked holes at lengths around the attention's 32-key step and
 64-query block; residual products split over K with two query tiles per wave, two
 passes, and hidden sizes above 4,096 and 8,192 (narrow stages of two layers, so
-that a split product's sums enter the next layer and the output); a row's result
+that a split product's sums enter the next layer and the output); hidden states
+at 2-byte aligned addresses; a row's result
 in a forward must be bitwise the same whichever product form its batch selects
 (16 rows or fewer, 17-32, 33-64).
 
@@ -100,6 +101,29 @@ def test_prompt_forms(dims, P0, n, holes, tiles, split):
         k, v = g.read(l, 0, P0, n)
         assert rel_err(host(k), o.K[l][0][:, P0:P0 + n]) <= TOL_STAGE
         assert rel_err(host(v), o.V[l][0][:, P0:P0 + n]) <= TOL_STAGE
+    p.close()
+
+
+@pytest.mark.parametrize("hidden", [256, 4104])
+def test_prompt_at_odd_addresses(hidden):
+    """hidden_in and hidden_out one element (2 bytes) past a 16-byte boundary: the
+    result is that of aligned ones, and the elements beside hidden_out stay."""
+    shape = synth.StageShape("odd", 16, n_layers=1, head_dim=128, hidden=hidden, n_q_heads=2, n_kv_heads=1, ffn=2048)
+    p = Pair(shape, 480, with_oracle=False)
+    n = 70
+    x = synth.make_hidden(shape, n, 480, 1).cuda()
+    outs = []
+    for off in (0, 1):
+        g, _ = p.states(1, 0, n, 480, with_oracle=False)
+        src, dst = (torch.full((n * hidden + 8,), 7.0, dtype=x.dtype, device="cuda") for _ in range(2))
+        view = src[off:off + n * hidden].view(n, hidden)
+        view.copy_(x)
+        p.gpu.prefill(g, np.arange(n), view, hidden_out=dst[off:off + n * hidden].view(n, hidden))
+        torch.cuda.synchronize()
+        outs.append(dst[off:off + n * hidden].cpu())
+        assert (dst[:off] == 7).all() and (dst[off + n * hidden:] == 7).all()
+        g.free()
+    assert torch.equal(*outs)
     p.close()
 
 

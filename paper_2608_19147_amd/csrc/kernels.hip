@@ -2560,7 +2560,7 @@ hipError_t launch_attention(const AttnArgs& a, int head_dim, int queries_per_ite
 // (1024 cycles for the eight waves' steps) take longer than the products (768),
 // so QTW = 2 where the prompt has workgroups enough.  Bound by vector instructions
 // (about 150 per tile and step beside 24 products) and the steps' barriers: 2048
-// tokens of 32 x 128 heads 240 -> about 85 us a layer, 517 after 1536 170 -> 84.
+// tokens of 32 x 128 heads 240 -> about 89 us a layer, 517 after 1536 170 -> 88.
 // Masked rows and rows past the block's last query enter as zeros with a -inf
 // score, and so, for each wave, do the rows of tokens past its last: a non-finite
 // row reaches no token before its group of 16 (a wave's 16 QTW query vectors lie
